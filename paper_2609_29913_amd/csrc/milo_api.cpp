@@ -268,7 +268,7 @@ int milo_cache_create(const milo_cache_desc* desc, const uint16_t* const* pk, co
   };
   hipError_t e = hipGetDevice(&c->device);
   if (e != hipSuccess) { c->device = -1; return cleanup_fail(hip_fail(e, "hipGetDevice")); }
-  if ((e = hipMalloc(&c->data, (size_t)c->data_elems * 2)) != hipSuccess)
+  if ((e = hipMalloc(&c->data, (size_t)c->data_elems * 2 + kOverread)) != hipSuccess)
     return cleanup_fail(hip_fail(e, "hipMalloc(packed factors)"));
   if (!src_on_device && (e = hipMalloc(&staging, (size_t)stage_elems * 2)) != hipSuccess)
     return cleanup_fail(hip_fail(e, "hipMalloc(staging)"));
@@ -599,7 +599,7 @@ class CacheWorkspace : public Workspace {
       if (cap >= 0 && c->data_elems * 2 + bytes > cap)
         return fail(MILO_ERR_OUT_OF_MEMORY, "reconstruction buffer of %lld bytes exceeds MILO_MAX_DEVICE_BYTES",
                     (long long)bytes);
-      MILO_HIP(hipMalloc(&c->recon_raw, (size_t)bytes));
+      MILO_HIP(hipMalloc(&c->recon_raw, (size_t)bytes + kOverread));
       // start a whole number of 1 KiB fragments from the factor buffer
       const uintptr_t raw = reinterpret_cast<uintptr_t>(c->recon_raw), base = reinterpret_cast<uintptr_t>(data);
       const uintptr_t adj = (base - raw) & 1023u;
@@ -808,21 +808,18 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
       std::memcpy(sch.bytes.data() + rb_off, rp.blocks.data(), rp.blocks.size() * sizeof(ReconBlock));
       std::memcpy(sch.bytes.data() + rt_off, rp.tasks.data(), rp.tasks.size() * sizeof(int2));
     }
-    const int max_rt = sch.max_own <= 2 ? 2 : sch.max_own == 3 ? 3 : 4;
-    // deepest fragment ring that fits next to the program, projected query and
-    // weight tile (4 slots go with the half weight tile)
+    // Kernel variant by the rank tiles a wave owns: up to two, the one that takes
+    // tiles in pairs (half the LDS reads per score); else the ones that take
+    // single tiles and fetch ahead for the gang.  Few columns that share P leave a
+    // step bound by how fast P comes from HBM, and there fetching ahead is worth
+    // more: 224 columns (7B layer, 8 requests) 56.2 us single against 59.8 in
+    // pairs, 640 (1M tokens, 16 requests) 1445 against 1501; at 896 columns 208
+    // against 198, with INT8 P (half the bytes) 57.2 against 53.4, on rebuilt
+    // blocks (640 columns) 287 against 281; a gang of one shares nothing.
+    int max_rt = sch.max_own <= 2 ? 2 : sch.max_own == 3 ? 3 : 4;
+    if (max_rt == 2 && sch.gang > 1 && n_cols <= kFetchAheadCols && !c->p_int8 && n_recon == 0 && !shared_tail) max_rt = 3;
     const size_t base = attend_lds_base_bytes(c->d, sch.rk_pad_max, sch.rv_pad_max, sch.half_w);
     const size_t prog = (size_t)sch.prog_bytes;
-    int nslot = 0;
-    if (sch.half_w) {
-      // the program was sized to leave room for this ring
-      if (prog + base + attend_ring_bytes(4) > (size_t)kLdsBytes)
-        return fail(MILO_ERR_UNSUPPORTED, "work schedule does not fit in LDS");
-      nslot = 4;
-    } else {
-      for (int cand : {8, 6})
-        if (prog + base + attend_ring_bytes(cand) <= (size_t)kLdsBytes) { nslot = cand; break; }
-    }
     // the workspace for the new plan's partials first (a workspace that cannot
     // hold them fails here, before anything is queued), then the upload, in
     // stream order: the kernels of earlier calls, queued before the copy, read
@@ -842,11 +839,10 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
     ps.count_off = sch.count_off;
     ps.tiles = til.geom;
     ps.max_rt = max_rt;
-    ps.nslot = nslot;
     ps.rk_pad_max = sch.rk_pad_max;
     ps.prog_bytes = sch.prog_bytes;
-    ps.ring_offset = (int)base;
-    ps.lds = prog + base + attend_ring_bytes(nslot);
+    ps.work_bytes = (int)base;
+    ps.lds = prog + base;
     ps.n_recon_blocks = (int)rp.blocks.size();
     ps.n_recon_tasks = (int)rp.tasks.size();
     ps.recon_blocks_off = rb_off;
@@ -854,6 +850,7 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
     ps.recon_elems = rp.elems;
     ps.tail_region = tail_region;
     ps.run_cap = sch.run_cap;
+    ps.gang = sch.gang;
     ps.tail_T_pad = tail_tiles * kTile;
     ps.gemv = gemv;
     ps.key.swap(key);
@@ -895,6 +892,7 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
   aa.data = c->data;
   aa.recon_delta = recon_delta;
   aa.run_cap = ps.run_cap;
+  aa.gang = ps.gang;
   aa.prog = ps.plan_d;
   aa.q = q;
   aa.tail_k = tail_k;
@@ -911,8 +909,10 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
   aa.n_block_slots = ps.n_block_slots;
   aa.qt_stride = ps.rk_pad_max + 8;
   aa.prog_bytes = ps.prog_bytes;
-  aa.ring_offset = ps.ring_offset;
+  aa.work_bytes = ps.work_bytes;
   aa.N_g = n_q * G;
+  aa.N_g_inv = (uint32_t)std::min<uint64_t>((1ull << 32) / aa.N_g, 0xffffffffu);
+  aa.G_inv = (uint32_t)std::min<uint64_t>((1ull << 32) / G, 0xffffffffu);
   aa.tl = tls;
   MergeArgs ma{};
   ma.part_o = part_o;
@@ -987,7 +987,7 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
   }
   for (int l = 0; l < ps.n_launch; ++l) {
     aa.wg = reinterpret_cast<const WgProgram*>(ps.plan_d) + (size_t)l * kCUs;
-    e = launch_attend(aa, c->d, ps.max_rt, ps.nslot, c->p_int8, ps.gemv, kCUs, ps.lds, s, l == 0 ? ev[0] : nullptr,
+    e = launch_attend(aa, c->d, ps.max_rt, c->p_int8, ps.gemv, kCUs, ps.lds, s, l == 0 ? ev[0] : nullptr,
                       l == ps.n_launch - 1 ? ev[1] : nullptr);
     if (e != hipSuccess) return launch_fail(e, "attend kernel launch");
   }

@@ -21,16 +21,17 @@ struct PlanState {
   std::vector<int32_t> key;  // call shape the plan was built for (empty: none)
   int64_t builds = 0;
   const unsigned char* plan_d = nullptr;  // device copy of the plan
-  int n_launch = 0, n_slots = 0, n_block_slots = 0, max_rt = 0, nslot = 0, rk_pad_max = 0, n_chunks = 0;
+  int n_launch = 0, n_slots = 0, n_block_slots = 0, max_rt = 0, rk_pad_max = 0, n_chunks = 0;
   TileGeom tiles{};
   int64_t count_off = 0;  // byte offset of the plan's slot counts
-  int prog_bytes = 0, ring_offset = 0;
+  int prog_bytes = 0, work_bytes = 0;
   size_t lds = 0;
   // reconstruct-then-attend: reconstructed blocks, their table and tasks in the plan
   int n_recon_blocks = 0, n_recon_tasks = 0;
   int64_t recon_blocks_off = 0, recon_tasks_off = 0;  // byte offsets in the plan
   int64_t recon_elems = 0;                            // reconstruction buffer (bf16 elements)
   bool gemv = false;                                  // latent projection as a wavefront GEMV
+  int gang = 1;                                       // workgroups per gang
   int run_cap = kRunCap;                              // run buffer entries of the plan
   int64_t tail_region = -1;                           // a prefill chunk's packed shared tail (or -1)
   int tail_T_pad = 0;                                 // its planned rows

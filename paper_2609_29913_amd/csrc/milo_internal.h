@@ -59,9 +59,11 @@ __host__ __device__ inline int owned_before(int nrt, int w, int n) {
 
 // Token segments of the latent value pass for a block with nrt rank tiles of
 // 32: the split (1, 2, 4 or 8 segments) with the least work for the busiest
-// wave, ties going to fewer segments (fewer partial sums to combine), with no wave
-// owning more than kMaxOwn rank tiles; past 8 * kMaxOwn rank tiles no split
-// qualifies and the block uses one segment (every wave owns nrt / 8 tiles).
+// wave, with no wave owning more than kMaxOwn rank tiles; past 8 * kMaxOwn rank
+// tiles no split qualifies and the block uses one segment (every wave owns
+// nrt / 8 tiles).  Ties go to fewer segments (fewer partial sums to combine),
+// except that two beat one: a wave with two rank tiles over half the tokens
+// reads half the weights from LDS.
 __host__ __device__ constexpr int v_segments(int nrt) {
   int best = 1, best_work = 1 << 30;
   for (int nseg = 1; nseg <= kWaves; nseg *= 2) {
@@ -69,7 +71,7 @@ __host__ __device__ constexpr int v_segments(int nrt) {
     const int own = (nrt + ng - 1) / ng;
     if (own > kMaxOwn) continue;
     const int work = own * (kTile / nseg);
-    if (work < best_work) {
+    if (work < best_work || (work == best_work && nseg == 2)) {
       best_work = work;
       best = nseg;
     }
@@ -394,8 +396,10 @@ static_assert(sizeof(WorkItem) == 80, "work item layout");
 // request i sees only its first tail_len_of(tl, i) tokens
 enum ItemFlags : int32_t { kItemFirst = 1, kItemFlush = 2, kItemInt8 = 4, kItemDense = 8, kItemCausal = 16 };
 // packed fields of a block item's flags: bits 8-9 lg_rank_groups of its block,
+// bits 10-14 the workgroup's place in its gang,
 // bits 16-21 the tile's column count - 1, bits 24-26 its KV head count - 1
 constexpr int kItemLgNgShift = 8;
+constexpr int kItemGangShift = 10;
 constexpr int kItemColsShift = 16;
 constexpr int kItemHeadsShift = 24;
 
@@ -404,8 +408,7 @@ constexpr int kItemHeadsShift = 24;
 // copied into LDS at kernel start.  Each wave derives, item by item, the runs
 // of consecutive packed fragments it consumes (a run is (first fragment index,
 // count); block_runs below), into a per-wave run buffer of kRunCap entries
-// that follows the items in LDS; after the last block item a sentinel run
-// (fragment 0, 2^30) feeds the look-ahead loads issued past the last fragment.
+// that follows the items in LDS.
 struct WgProgram {
   int64_t off;                // byte offset in the program buffer (16-byte aligned)
   int32_t words;              // program size in 4-byte words
@@ -413,7 +416,9 @@ struct WgProgram {
   int32_t pad[2];
 };
 static_assert(sizeof(WgProgram) == 24, "program entry layout");
-constexpr int kSentinelRun = 1 << 27;  // a bf16 run long enough for any look-ahead
+// Bytes the attention kernel's fragment loads may read past the end of a run:
+// the factor and reconstruction buffers are allocated that much longer.
+constexpr int kOverread = 8 * 1024;
 
 // Attention kernel geometry.
 constexpr int kThreads = 64 * kWaves;
@@ -421,7 +426,12 @@ constexpr int kCols = 64;                      // query columns per workgroup
 constexpr int kGemvCols = 16;                  // most columns of a tile whose projection may run as a GEMV
 constexpr int kTokWave = kTile / kWaves;       // tokens per wave per tile (one MFMA row block)
 static_assert(kTokWave == 32, "the score pass gives every wave one 32-token sub-tile");
-constexpr int kWStride = kTile + 8;            // bf16 row stride of the weight tile in LDS
+constexpr int kWStride = kTile + 8;            // bf16 row stride of one tile's weights in LDS
+constexpr int kWStridePair = 2 * kTile + 8;    // of two tiles' weights
+// Where every block of a plan has ranks up to kPairRank the kernel takes two
+// 256-token tiles per step (no wave then owns more than kMaxOwn rank tiles).
+constexpr int kPairRank = 32 * kWaves * kMaxOwn;
+constexpr int kFetchAheadCols = 768;           // most columns of a step that takes single tiles at ranks <= kPairRank
 constexpr int kMaxGroup = 16;                  // max query heads per KV head
 constexpr int kMaxRank = 896;                  // largest rank of the latent route (LDS bound)
 constexpr int kMaxStoredRank = 1024;           // largest rank a cache stores (higher-rank blocks are reconstructed)
@@ -496,9 +506,11 @@ struct AttendArgs {
   int n_block_slots;         // slots [0, n_block_slots) hold block groups, the rest tail chunks
   int qt_stride;             // bf16 row stride of the projected query in LDS
   int prog_bytes;            // LDS bytes reserved for the program (the work area follows)
-  int ring_offset;           // byte offset of the per-wave fragment rings in the work area
+  int work_bytes;            // bytes of the work area
   int N_g;                   // query columns per KV head, n_q * G
+  uint32_t N_g_inv, G_inv;   // floor(2^32 / N_g), floor(2^32 / G) (at most 2^32 - 1)
   int recon_delta;           // fragments from `data` to the reconstruction buffer (dense items)
+  int gang;                  // workgroups that share a block's P (kItemGangShift)
   int run_cap;               // entries of a run buffer (the plan's bound, <= kRunCap)
   TailLens tl;               // tail lengths of this call
 };
@@ -543,7 +555,7 @@ hipError_t launch_scale_units(const float* ks, const float* vs, int T_pad, float
 // (hipExtLaunchKernelGGL), so they time the kernel itself.
 // gemv: the kernel variant whose latent projection is a wavefront GEMV (tiles
 // of at most kGemvCols columns; bf16 P factors only)
-hipError_t launch_attend(const AttendArgs& a, int head_dim, int max_rt, int nslot, bool p_int8, bool gemv, int grid,
+hipError_t launch_attend(const AttendArgs& a, int head_dim, int max_rt, bool p_int8, bool gemv, int grid,
                          size_t lds_bytes, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_merge(const MergeArgs& a, int head_dim, int n_cols, hipStream_t s, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr);
@@ -561,9 +573,9 @@ hipError_t launch_pack_tail(const TailPackArgs& a, int head_dim, hipStream_t s);
 // Reconstruction of the dense blocks of a call: one workgroup per task.
 hipError_t launch_recon(const ReconArgs& a, int head_dim, int n_tasks, hipStream_t s, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr);
-// LDS of the attention kernel: a base region (projected query, weight tile and
-// reductions, or the tail item's buffers) followed by kWaves rings of nslot fragments.
+// LDS of the attention kernel's work area: projected query, weight tile and
+// reductions, or the up-projection's or the tail item's buffers.
 size_t attend_lds_base_bytes(int head_dim, int rk_pad_max, int rv_pad_max, bool half_w);
-size_t attend_ring_bytes(int nslot);
+size_t attend_ring_bytes(int nslot);  // 0: fragments stream through registers
 
 }  // namespace milo

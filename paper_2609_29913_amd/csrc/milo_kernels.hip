@@ -27,6 +27,8 @@
 // is one v_exp_f32.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "milo_internal.h"
 
 namespace milo {
@@ -67,72 +69,48 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t u) {
   return __uint_as_float(static_cast<uint32_t>(u) << 16);
 }
 
+// sixteen zeros set where they stand (opaque to the optimiser, which would
+// otherwise keep one zero accumulator live across the loops that need it)
+__device__ __forceinline__ f32x16 zero16() {
+  float z;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+  f32x16 v;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = z;
+  return v;
+}
+
+// v, as a value the optimiser cannot trace: addresses derived from it are formed
+// where they are used instead of staying live across a loop
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// ends x's life without an instruction: its registers are free until the next write
+__device__ __forceinline__ void forget(bf16x8& x) { asm volatile("" : "=v"(x)); }
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// n / d for a divisor whose floor(2^32 / d) (2^32 - 1 for d = 1) the host
+// computed: the product is at most one short (n < 2^32)
+__device__ __forceinline__ int div_by(int n, int d, uint32_t m) {
+  const int q = (int)__umulhi((uint32_t)n, m);
+  return n - q * d >= d ? q + 1 : q;
+}
 // query row i * H_q + h of head-major column c = g * N_g + i * G + (h mod G)
-__device__ __forceinline__ int64_t query_row(int c, int N_g, int G, int H_q) {
-  const int g = c / N_g, rem = c - g * N_g, i = rem / G;
-  return (int64_t)i * H_q + g * G + (rem - i * G);
-}
-
-// Direct global->LDS load of one fragment: lane l's 16 bytes from `src` land at
-// LDS byte address lds_slot + 16 l.  Issued as inline assembly, so the compiler
-// neither counts it nor orders other LDS accesses after it; every consumer
-// waits for it explicitly (wait_vmcnt) before reading the slot.  M0 carries the
-// slot address; no compiler-generated code in these kernels uses M0.
-__device__ __forceinline__ void lds_dma16(const void* src, uint32_t lds_slot) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_slot), "v"(src) : "memory");
-}
-
-// LDS reads of the workgroup's program (run lists, work items).  The compiler
-// cannot tell these addresses from the slots that in-flight global->LDS loads
-// write, so a plain LDS load here would make it wait for every outstanding
-// fragment load; the program region is never a load target, so the reads are
-// issued directly, waiting only for themselves.
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)reinterpret_cast<uintptr_t>(p);  // offset within the LDS aperture
-}
-__device__ __forceinline__ int2 prog_read_b64(const void* p) {
-  int2 v;
-  asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_addr(p)));
-  return v;
-}
-__device__ __forceinline__ int4 prog_read_b128(const void* p) {
-  int4 v;
-  asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_addr(p)));
-  return v;
-}
-
-// LDS stores the compiler would otherwise order after every in-flight
-// global->LDS fragment load (it cannot prove they target other addresses).
-__device__ __forceinline__ void lds_store_b128(void* p, float4 v) {
-  const f32x4 x = {v.x, v.y, v.z, v.w};
-  asm volatile("ds_write_b128 %0, %1" ::"v"(lds_addr(p)), "v"(x) : "memory");
-}
-__device__ __forceinline__ void lds_store_b64(void* p, int2 v) {
-  asm volatile("ds_write_b64 %0, %1" ::"v"(lds_addr(p)), "v"(v) : "memory");
-}
-__device__ __forceinline__ void lds_store_b32(void* p, float v) {
-  asm volatile("ds_write_b32 %0, %1" ::"v"(lds_addr(p)), "v"(v) : "memory");
+__device__ __forceinline__ int64_t query_row(const AttendArgs& a, int c) {
+  const int g = div_by(c, a.N_g, a.N_g_inv), rem = c - g * a.N_g, i = div_by(rem, a.G, a.G_inv);
+  return (int64_t)i * a.H_q + g * a.G + (rem - i * a.G);
 }
 
 // Workgroup barrier for the attention kernel: every wave's LDS reads and
-// writes issued before it are complete.  In-flight global->LDS fragment loads
-// are deliberately not waited for (each targets its own wave's ring slots);
-// __syncthreads() would make the compiler drain them (vmcnt(0)) at many
-// barriers.  The "memory" clobber keeps the compiler from moving memory
-// accesses across it.
+// writes issued before it are complete.  Global loads in flight (the waves'
+// fragment streams) are deliberately not waited for; __syncthreads() would
+// drain them (vmcnt(0)).  The "memory" clobber keeps the compiler from moving
+// memory accesses across it.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Wait until at most N vector-memory operations of this wave are outstanding
-// (they complete in issue order).  The "memory" clobber keeps LDS reads of the
-// slots it guards after it.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 16, "vmcnt immediate");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // ---------------------------------------------------------------------------
@@ -371,168 +349,161 @@ __device__ __forceinline__ void tail_item(const AttendArgs& a, const WorkItem& i
 // a work item read from LDS into wave-uniform registers
 __device__ __forceinline__ WorkItem lds_item(const unsigned char* p) {
   static_assert(sizeof(WorkItem) == 80, "a work item is five 16-byte chunks");
-  int4 v0, v1, v2, v3, v4;
-  const uint32_t a = lds_addr(p);
-  asm volatile(
-      "ds_read_b128 %0, %5\n\tds_read_b128 %1, %5 offset:16\n\tds_read_b128 %2, %5 offset:32\n\t"
-      "ds_read_b128 %3, %5 offset:48\n\tds_read_b128 %4, %5 offset:64\n\ts_waitcnt lgkmcnt(0)"
-      : "=&v"(v0), "=&v"(v1), "=&v"(v2), "=&v"(v3), "=&v"(v4)  // early clobber: the address
-      : "v"(a));                                                // must survive the first reads
-  const int4 vv[5] = {v0, v1, v2, v3, v4};
   int32_t w[20];
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
-    w[4 * i + 0] = __builtin_amdgcn_readfirstlane(vv[i].x);
-    w[4 * i + 1] = __builtin_amdgcn_readfirstlane(vv[i].y);
-    w[4 * i + 2] = __builtin_amdgcn_readfirstlane(vv[i].z);
-    w[4 * i + 3] = __builtin_amdgcn_readfirstlane(vv[i].w);
+    const int4 v = reinterpret_cast<const int4*>(p)[i];
+    w[4 * i + 0] = __builtin_amdgcn_readfirstlane(v.x);
+    w[4 * i + 1] = __builtin_amdgcn_readfirstlane(v.y);
+    w[4 * i + 2] = __builtin_amdgcn_readfirstlane(v.z);
+    w[4 * i + 3] = __builtin_amdgcn_readfirstlane(v.w);
   }
   WorkItem it;
   __builtin_memcpy(&it, w, sizeof(WorkItem));
   return it;
 }
 
-// A wave's fragment stream over all block items of its workgroup: the runs of
-// consecutive packed fragments in the order the wave consumes them (per block
-// item: its R^K run for the projection, then for every 256-token tile its P^K
-// run and its P^V run, then its R^V run for the up-projection; block_runs).
-// Wave 0 derives them item by item for all waves (RunDeriver below) into four
-// LDS run buffers per wave used in turn (entry (x, n): n consecutive fragments
-// from fragment x; (x, 0) ends a buffer), staying two block items ahead of the
-// item being computed: every item gives every wave at least three fragments
-// and the look-ahead loads run at most kDepth <= 6 fragments ahead, so they
-// never reach a buffer that is not ready, and the buffer being refilled is two
-// items behind.  Runs are read when their first fragment is issued.  After the
-// last block item a long sentinel run follows.  With NSLOT > 0 fragments reach the wave through a private ring of NSLOT LDS
-// slots, filled by direct global->LDS loads issued kDepth fragments ahead of
-// use, so every wait is a constant vmcnt; the look-ahead crosses item
-// boundaries, so the next item's first fragments load while the current one
-// finishes.  With NSLOT == 0 fragments are loaded straight into registers.
-template <int D, int NSLOT, bool I8>
-struct FragRing {
-  static constexpr int kDepth = NSLOT > 2 ? NSLOT - 2 : 1;  // units in flight
-  static_assert(kDepth <= 6, "run buffers are derived two block items (>= 6 units) ahead");
-  const unsigned char* data;  // packed factor buffer
-  int lane;                   // this lane
-  __bf16* ring;               // this wave's NSLOT slots
-  uint32_t ring_lds;          // LDS byte address of slot 0 (wave-uniform)
-  const int2* run;            // current entry of the run buffers (LDS)
-  int2* rbuf;                 // this wave's kRunBufs run buffers of run_cap entries
-  int run_cap;
-  int rb;                     // buffer the stream reads
-  int64_t off;                // byte offset of the next unit
-  int left;                   // units left in the current run
-  int step;                   // bytes per unit of the current run (1 KiB, or 256 for scale units)
-  int lane_off;               // this lane's byte offset in a unit of the current run
-  int rs, ws;                 // ring slots: next to read, next to fill
-  bf16x8 held;                // the second fragment of the last int8 unit taken
-  bool have_held;
-
-  __device__ __forceinline__ void load_run() {
-    int2 v = prog_read_b64(run);
-    if (__builtin_amdgcn_readfirstlane(v.y) == 0) {  // end of a buffer: the next one
-      rb = (rb + 1) % kRunBufs;
-      run = rbuf + rb * run_cap;
-      v = prog_read_b64(run);
-    }
-    const int x = __builtin_amdgcn_readfirstlane(v.x), n = __builtin_amdgcn_readfirstlane(v.y);
-    if constexpr (!I8) {  // every run holds bf16 fragments
-      off = (int64_t)x * (kFragElems * 2);
-      left = n;
-      return;
-    }
-    const int kind = (n >> kRunKindShift) & 3, count = n & kRunCountMask;
-    if (kind == kRunBf16) {
-      off = (int64_t)x * (kFragElems * 2);
-      left = count;
-      step = kFragElems * 2;
-      lane_off = 16 * lane;
-    } else if (kind == kRunI8) {  // two 512-byte fragments per unit
-      off = (int64_t)x * (kFragElems);
-      left = count >> 1;
-      step = kFragElems * 2;
-      lane_off = 16 * lane;
-    } else {  // scale unit: 256 bytes, every group of 16 lanes loads all of it
-      off = (int64_t)x * kScaleUnitBytes;
-      left = count;
-      step = kScaleUnitBytes;
-      lane_off = 16 * (lane & 15);
-    }
-  }
-  // the unit's start, and this lane's address in the next unit; advances the stream
-  __device__ __forceinline__ const unsigned char* next(const unsigned char** unit = nullptr) {
-    if (left == 0) {
-      ++run;
-      load_run();
-    }
-    const unsigned char* u = data + off;
-    if (unit) *unit = u;
-    --left;
-    if constexpr (!I8) {
-      off += kFragElems * 2;
-      return u + 16 * lane;
-    } else {
-      off += step;
-      return u + lane_off;
-    }
-  }
-  __device__ __forceinline__ void start() {
-    rb = 0;
-    run = rbuf;
-    load_run();
-    rs = 0;
-    ws = 0;
-    have_held = false;
-    if constexpr (NSLOT > 0) {
-#pragma unroll
-      for (int k = 0; k < kDepth; ++k) lds_dma16(next(), ring_lds + k * kFragElems * 2);
-      ws = kDepth;
-    }
-  }
-  // the slot (LDS) or unit (global memory) of the next unit, and advance
-  __device__ __forceinline__ const unsigned char* next_unit() {
-    if constexpr (NSLOT > 0) {
-      wait_vmcnt<kDepth - 1>();
-      const unsigned char* slot = reinterpret_cast<const unsigned char*>(ring + rs * kFragElems);
-      lds_dma16(next(), ring_lds + ws * kFragElems * 2);
-      rs = rs + 1 == NSLOT ? 0 : rs + 1;
-      ws = ws + 1 == NSLOT ? 0 : ws + 1;
-      return slot;
-    } else {
-      const unsigned char* u;
-      next(&u);
-      return u;
-    }
-  }
-  // the next bf16 fragment, in this lane's operand layout
-  __device__ __forceinline__ bf16x8 take() {
-    return ld_bf16x8(next_unit() + 16 * lane);
-  }
-  // the next fragment of an int8 run, converted to bf16 (exact: |code| <= 127);
-  // a unit holds two fragments, the second is kept for the following call
-  __device__ __forceinline__ bf16x8 take_i8() {
-    static_assert(I8, "int8 fragments only in the INT8 instantiation");
-    if (have_held) {
-      have_held = false;
-      return held;
-    }
-    const unsigned char* u = next_unit();
-    const uint2 lo = *reinterpret_cast<const uint2*>(u + 8 * lane);
-    const uint2 hi = *reinterpret_cast<const uint2*>(u + kFragElems + 8 * lane);
-    held = i8_to_bf16x8(hi);
-    have_held = true;
-    return i8_to_bf16x8(lo);
-  }
-  // the next scale unit: 32 K then 32 V scales (fp32); the pointer stays valid
-  // until the next take
-  __device__ __forceinline__ const float* take_scales() {
-    return reinterpret_cast<const float*>(next_unit());
-  }
+// A wave's fragment streams.  Fragments go from global memory straight into
+// registers, each in its lane's MFMA operand layout, through two sets of slots
+// that run ahead of the MFMAs: `ks` for R^K and P^K (projection and scores),
+// `vs` for P^V (value pass).  A run of n steps ends on the last slot of a set of
+// N: step f sits in slot (f - n) mod N, so a run takes first its n mod N odd
+// steps from the last slots, then whole rounds from slot 0, and each slot is
+// reloaded as it is consumed, with the step a round later or, past the run's
+// end, with its step of the next run of that set (the next tiles, or the next
+// item's first run).  Loads are issued in the order of use on every path, which
+// is what lets the compiler wait for the slot in use alone (s_waitcnt vmcnt
+// counts in order).  The set sizes are what the registers hold without a spill:
+// a spilled value's scratch loads sit in the same in-order count and stop the
+// streams.  Reloads may read past a run: at most kOverread bytes, which the
+// buffers' allocations cover.
+// (Streaming through per-wave LDS rings by direct global->LDS loads, as this
+// kernel did before, cost two LDS passes and ~16 scalar instructions per
+// fragment.)
+//
+// kPair (at most two latent rank tiles per wave, ranks up to 512): tiles are
+// taken two at a time, every wave scoring 64 tokens, so that one LDS read of a
+// Qt operand feeds two MFMAs.  With 32 tokens per wave the eight waves ask LDS
+// for 128 bytes per clock, all it has, as soon as the MFMAs run back to back.
+// Above that rank neither the registers nor LDS hold two tiles.
+template <int D, int MAX_RT>
+struct Streams {
+  static constexpr bool kPair = MAX_RT == 2;
+  static constexpr int KD = 4;               // steps in a round of ks
+  static constexpr int NS = kPair ? 2 : 1;   // fragments per step: token sub-tiles, or R^K steps i and i + KD
+  static constexpr int VD = 4;               // P^V fragments loaded ahead across tiles
+  static_assert(KD * 1024 <= kOverread, "reads past a run stay inside its buffer");
+  bf16x8 ks[KD][NS], vs[VD];
 };
 
-// Derivation of the fragment runs, done by wave 0 for all eight waves (lane w
+// f(integral constant i) for i = FROM, FROM + STEP, .. below TO
+template <int FROM, int TO, int STEP, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (FROM < TO) {
+    f(std::integral_constant<int, FROM>{});
+    static_for<FROM + STEP, TO, STEP>(f);
+  }
+}
+
+// A wave-uniform fragment address p + off loaded by every lane: buffer loads
+// take the base and offset in scalar registers, the lane's part in one vector
+// register.  wanted is -1, or 0: nothing is read (an empty buffer), the slot
+// gets zeros; as arithmetic on a scalar it costs no branch in the loops.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t frag_buffer(const unsigned char* p, int wanted) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(p), 0, __builtin_amdgcn_readfirstlane(wanted),
+                                           0x00020000);
+}
+// -1 where a < b (both far from the ends of the int range), else 0
+__device__ __forceinline__ int mask_lt(int a, int b) { return (a - b) >> 31; }
+__device__ __forceinline__ bf16x8 load_frag16(const unsigned char* p, int off, int lane16, int wanted = -1) {
+  return __builtin_bit_cast(bf16x8,
+                            __builtin_amdgcn_raw_buffer_load_b128(frag_buffer(p, wanted), lane16, off, 0));
+}
+__device__ __forceinline__ uint2 load_frag8(const unsigned char* p, int off, int lane8, int wanted) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(frag_buffer(p, wanted), lane8, off, 0));
+}
+// Where the slots of a set of N find their first steps of a run of n steps at p
+// (fragments of B bytes): slot s holds step (s + n) mod N, and in its second
+// fragment (kPair) what lies delta bytes on.  n = 0: no run.
+template <int N, int B>
+struct RunStart {
+  const unsigned char* p;
+  int odd, wanted, delta, wanted2;
+  __device__ __forceinline__ RunStart(const unsigned char* p_, int n, int delta_, int wanted2_)
+      : p(p_), odd(n & (N - 1)), wanted(mask_lt(0, n)), delta(delta_), wanted2(wanted2_) {}
+  __device__ __forceinline__ int off(int s) const { return (s + odd - (s + odd >= N ? N : 0)) * B; }
+};
+// Consume a run of n steps (an even number) at p, whose second fragments lie
+// delta bytes on (wanted2: -1, or 0 for none), through slots 0 .. N-1: use(f, s)
+// takes slot s for step f + s, load(s, q, off, wanted, delta, wanted2) reloads it
+// from q + off; next: the set's next run.  The odd steps before the whole rounds
+// are one straight piece of code per count, so that their operand reads overlap;
+// step by step behind branches they cost as much as two rounds.
+template <int N, int B, typename Use, typename Load>
+__device__ __forceinline__ void consume_run(const unsigned char* p, int n, int delta, int wanted2,
+                                            const RunStart<N, B>& next, Use&& use, Load&& load) {
+  const int odd = n & (N - 1);
+  const bool more = n >= N;
+  static_for<2, N, 2>([&](auto odd_c) {
+    constexpr int ODD = decltype(odd_c)::value;
+    if (odd != ODD) return;
+    if (!more) {  // a run shorter than a round: the slots it leaves out move on too
+      static_for<0, N - ODD, 1>([&](auto s) { load(s, next.p, next.off(s), next.wanted, next.delta, next.wanted2); });
+    }
+    const unsigned char* q = more ? p : next.p;
+    const int wanted = mask_lt(N - 1, n) | next.wanted, d = more ? delta : next.delta;
+    const int w2 = more ? wanted2 : next.wanted2;
+    static_for<N - ODD, N, 1>([&](auto s) {
+      use(ODD - N, s);
+      load(s, q, more ? (ODD + s) * B : next.off(s), wanted, d, w2);
+    });
+  });
+#pragma clang loop unroll(disable)
+  for (int f = odd; f < n; f += N) {
+    const bool last = f + N >= n;
+    const int wanted = mask_lt(f + N, n) | next.wanted;
+    const unsigned char* q = last ? next.p : p;
+    const int lo = last ? next.odd * B : (f + N) * B, hi = last ? lo - N * B : lo, wrap = N - next.odd;
+    const int d = last ? next.delta : delta, w2 = last ? next.wanted2 : wanted2;
+    static_for<0, N, 1>([&](auto s) {
+      use(f, s);
+      load(s, q, (s < wrap ? lo : hi) + s * B, wanted, d, w2);
+    });
+  }
+}
+
+// The first run of a block item (bf16 P factors) for wave `wave`, at p: R^K if
+// the wave owns projection rank tiles, else the first tiles' P^K
+template <int D, int MAX_RT>
+__device__ __forceinline__ RunStart<Streams<D, MAX_RT>::KD, kFragElems * 2> item_first_run(const WorkItem* it, int wave,
+                                                                                             const unsigned char* p) {
+  constexpr int B = kFragElems * 2, KD = Streams<D, MAX_RT>::KD;
+  const int rk_pad = __builtin_amdgcn_readfirstlane(it->blk.rk_pad), ntile = __builtin_amdgcn_readfirstlane(it->ntile);
+  const bool dense = (__builtin_amdgcn_readfirstlane(it->flags) & kItemDense) != 0;
+  const bool rk = !dense && owned_tiles(rk_pad >> 5, wave, kWaves) > 0;
+  return RunStart<KD, B>(p, rk ? KD : rk_pad >> 4, rk ? KD * B : (rk_pad >> 4) * B,
+                         rk ? -(int)(D / 16 > KD) : mask_lt(1, ntile));
+}
+
+// The waves' run lists: for each of its block items a wave finds the first
+// fragment of the runs it consumes (block_runs) in an LDS buffer that wave 0
+// fills for all eight waves (RunDeriver) two block items ahead, four buffers
+// used in turn: the buffer being refilled is two items behind, and the next
+// item's list is complete while the current item runs.  After the last block
+// item a run of the buffer's first fragments follows (loaded, never used).
+struct RunList {
+  const int2* rbuf;  // this wave's kRunBufs buffers of run_cap entries
+  int run_cap, rb;   // entries per buffer; the current item's buffer
+  __device__ __forceinline__ int first(int k) const { return __builtin_amdgcn_readfirstlane(rbuf[rb * run_cap + k].x); }
+  __device__ __forceinline__ int next_first() const {
+    return __builtin_amdgcn_readfirstlane(rbuf[((rb + 1) % kRunBufs) * run_cap].x);
+  }
+  __device__ __forceinline__ void advance() { rb = (rb + 1) % kRunBufs; }
+};
+
+// Derivation of the run lists, done by wave 0 for all eight waves (lane w
 // derives wave w's runs, in vector registers): the runs of the workgroup's
-// next block item, or the sentinel run after the last one, into every wave's
+// next block item, or the closing run after the last one, into every wave's
 // buffer gb.  Runs are read by their wave only after a later workgroup
 // barrier.
 template <int D>
@@ -559,35 +530,40 @@ struct RunDeriver {
     if (lane < kWaves) {
       int2* out = rbuf + ((size_t)lane * kRunBufs + gb) * run_cap;
       int n = 0;
-      auto put = [&](int x, int cnt) {
-        lds_store_b64(out + n, make_int2(x, cnt));
-        ++n;
-      };
+      auto put = [&](int x, int cnt) { out[n++] = make_int2(x, cnt); };
       if (found)
         block_runs(it.blk, it.g, ((it.flags >> kItemHeadsShift) & 7) + 1, it.tile0, it.ntile, lane, D,
                    (it.flags >> kItemLgNgShift) & 3, (it.flags & kItemInt8) != 0, put, (it.flags & kItemDense) != 0,
                    recon_delta);
-      else put(0, kSentinelRun);
-      put(0, 0);
+      else put(0, 0);
     }
     gb = (gb + 1) % kRunBufs;
   }
 };
 
 // A workgroup's running partial for its current group of block items (one KV
-// head and column tile): the output in the up-projection's lane layout (NCB
-// 16-column blocks of the wave's 16-dim slice), the per-column maximum in the
-// score layout (32 ch + lane % 32; every wave holds it), the per-column sum
-// in wave 0 (thread t: column t).
-template <int NCB>
+// head and column tile): the per-column maximum in the score layout (32 ch +
+// lane % 32; every wave holds it) and the per-column sum in wave 0 (thread t:
+// column t).  The output is folded in place in the group's slot, each thread
+// reading back what it wrote (registers for it would spill the tile loop).
 struct GroupAcc {
-  f32x4 o[NCB];
   float m[2];
   float l;
 };
+// 16-byte chunks of an item's query rows a thread loads, and the load: chunk x
+// of the 64 rows of a column tile (first column c0, cn columns)
 template <int D>
-constexpr int up_col_blocks() {
-  return 4 * (D / 16) / kWaves;  // 16-column blocks per wave in the up-projection
+constexpr int query_loads() {
+  return kCols * (D / 8) / kThreads;
+}
+template <int D>
+__device__ __forceinline__ void load_queries(const AttendArgs& a, int c0, int cn, int tid,
+                                             bf16x8 (&qv)[query_loads<D>()]) {
+#pragma unroll
+  for (int u = 0; u < query_loads<D>(); ++u) {
+    const unsigned x = opaque(tid) + u * kThreads, cl = x / (D / 8), j = x % (D / 8);
+    qv[u] = ld_bf16x8(a.q + query_row(a, c0 + min((int)cl, cn - 1)) * D + 8 * j);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -605,21 +581,24 @@ constexpr int up_col_blocks() {
 // sums are then combined in LDS and the latent result goes to LDS as bf16.
 // Up-projection: each wave computes a 16-dim slice of the output for all 64
 // columns over all ranks.  Every factor fragment a wave consumes (R^K for the
-// projection, P^K and P^V per tile, R^V for the up-projection) comes from the
-// wave's fragment stream (FragRing above); the item's queries are loaded into
-// LDS at its start.  Every loop is software-pipelined: the operands of step
-// k+1 are read while the MFMAs of step k run.
+// projection, P^K and P^V per tile, R^V for the up-projection) comes through
+// the wave's register slots (Streams above); the item's queries are loaded into
+// LDS at its start.
 // ---------------------------------------------------------------------------
 // MODE: 0 bf16 P factors, 1 INT8 P factors, 2 bf16 P factors with the
 // projection as a wavefront GEMV (kernel variants, so no branch of one costs
 // the others registers)
-template <int D, int MAX_RT, int NSLOT, bool WH, int MODE>
+template <int D, int MAX_RT, int MODE>
 __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& it, unsigned char* smem,
-                                           FragRing<D, NSLOT, MODE == 1>& fr, RunDeriver<D>& rd,
-                                           GroupAcc<up_col_blocks<D>()>& acc, const int tid) {
+                                           Streams<D, MAX_RT>& fs, RunList& rl, RunDeriver<D>& rd,
+                                           GroupAcc& acc, bf16x8 (&qv)[query_loads<D>()], const WorkItem* next_item,
+                                           const int tid) {
   constexpr bool I8 = MODE == 1, GV = MODE == 2;
   constexpr int NK = D / 16;
-  constexpr int kORed = 4;  // partial-output slots of the up-projection reduction
+  constexpr int KD = Streams<D, MAX_RT>::KD;
+  constexpr int NS = Streams<D, MAX_RT>::NS, VD = Streams<D, MAX_RT>::VD;
+  constexpr bool kPair = Streams<D, MAX_RT>::kPair;
+  static_assert(NK == KD || NK == 2 * KD, "an R^K rank tile is one or two rounds");
   const BlockMeta& bm = it.blk;
   const int slot = it.slot, g0 = it.g, c0 = it.req;
   const int cn = ((it.flags >> kItemColsShift) & 63) + 1;  // columns of the tile
@@ -642,56 +621,131 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
   const int own_v = owned_tiles(nrt_v, rg, ng);
   const int nst = 16 / nseg;                // 16-token steps of the wave's segment per tile
   const int T = bm.T;
+  constexpr int kTouches = kPair ? 0 : 2;  // lines a lane fetches ahead for the gang per tile
+  const int gang_at = (it.flags >> kItemGangShift) & 31;
   const int ntiles = it.ntile, tile0 = it.tile0;  // tiles this item covers
   // causal limits of this lane's two columns (32 ch + lane % 32; request (c mod N_g) / G)
   // and the smallest over the tile (wave-uniform), past which tokens need masking
   int lim[2] = {T, T}, lim_min = T;
   if (causal) {
 #pragma unroll
-    for (int ch = 0; ch < 2; ++ch)
-      lim[ch] = tail_len_of(a.tl, ((c0 + min(32 * ch + (lane & 31), cn - 1)) % N_g) / G);
+    for (int ch = 0; ch < 2; ++ch) {
+      const int c = c0 + min(32 * ch + (lane & 31), cn - 1);
+      lim[ch] = tail_len_of(a.tl, div_by(c - div_by(c, N_g, a.N_g_inv) * N_g, G, a.G_inv));
+    }
     lim_min = min(lim[0], lim[1]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) lim_min = min(lim_min, __shfl_xor(lim_min, off));
   }
-  __bf16* qt = reinterpret_cast<__bf16*>(smem);              // [kCols][qsd]
-  // the weight tile: [kCols][kWS] bf16, all 256 tokens of a tile, or (WH) one
-  // 128-token half at a time when LDS is short (ranks above 512)
-  constexpr int kWS = WH ? kTile / 2 + 8 : kWStride;
-  __bf16* wl = qt + kCols * qsd;                          // [kCols][kWS]
+  __bf16* qt = reinterpret_cast<__bf16*>(smem);             // [kCols][qsd]
+  constexpr int kWS = kPair ? kWStridePair : kWStride;
+  __bf16* wl = qt + kCols * qsd;                            // [kCols][kWS] the weights of one or two tiles
   float* red = reinterpret_cast<float*>(wl + kCols * kWS);  // [kWaves][kCols]
-  // the wave's next fragment; the order of take() calls below is the order of
-  // the wave's runs: R^K (waves that own projection rank tiles), then per tile
-  // P^K and P^V, then R^V
-  auto take = [&]() -> bf16x8 { return fr.take(); };
-  // P^K / P^V fragments: bf16, or int8 codes converted exactly (INT8 P factors)
-  auto take_p = [&]() -> bf16x8 {
-    if constexpr (I8) return fr.take_i8();
-    else return fr.take();
+  float* units = red + kWaves * kCols + wave * 128;         // kPair, INT8: the wave's scale units of two tiles
+
+  // the runs of this item (first unit of each; P^K and P^V of consecutive tiles
+  // follow at constant strides) and the first run of the next one
+  const unsigned char* data = reinterpret_cast<const unsigned char*>(a.data);
+  constexpr int kFragBytes = kFragElems * 2;
+  constexpr int kPBytes = I8 ? kFragElems : kFragElems * 2;  // a P^K / P^V fragment
+  const int n_rk = own_k > 0 && !dense ? nh : 0, per_tile = 1 + (I8 ? 1 : 0) + (own_v > 0 ? 1 : 0);
+  const unsigned char* rkp = data + (int64_t)rl.first(0) * kFragBytes;
+  const unsigned char* pkp = data + (int64_t)rl.first(n_rk) * kPBytes;
+  const unsigned char* pvp = data + (own_v > 0 ? (int64_t)rl.first(n_rk + 1 + (I8 ? 1 : 0)) * kPBytes : 0);
+  const unsigned char* scp = data + (I8 ? (int64_t)rl.first(n_rk + 1) * kScaleUnitBytes : 0);
+  const RunStart<KD, kPBytes> pk_first(pkp, nks, nks * kPBytes, mask_lt(1, ntiles));
+  const int lane16 = 16 * lane;
+  auto ldf = [&](const unsigned char* p, int off, int wanted = -1) {  // a bf16 fragment
+    return load_frag16(p, off, lane16, wanted);
+  };
+  // a P^K / P^V fragment: bf16, or int8 codes (converted exactly as they are used)
+  auto ldp = [&](const unsigned char* p, int off, int wanted = -1) {
+    if constexpr (I8) {
+      const uint2 v = load_frag8(p, off, lane16 >> 1, wanted);
+      return __builtin_bit_cast(bf16x8, make_uint4(v.x, v.y, 0, 0));
+    } else {
+      return load_frag16(p, off, lane16, wanted);
+    }
+  };
+  auto use_p = [&](const bf16x8& x) {
+    if constexpr (I8) {
+      const uint4 v = __builtin_bit_cast(uint4, x);
+      return i8_to_bf16x8(make_uint2(v.x, v.y));
+    } else {
+      return x;
+    }
+  };
+  // f(rank tiles this wave owns in the value pass, 16-token steps in a round of
+  // it), as integral constants: a round is up to eight fragments, the first VD
+  // of them loaded across tiles (vs), the rest within a tile.  A wave owns three
+  // tiles or more only in a single segment of 16 steps (v_segments)
+  static_assert(v_segments(1) == 8 && v_segments(2) == 4 && v_segments(3) == 2 && v_segments(4) == 2 &&
+                v_segments(5) == 2 && v_segments(8) == 2 && v_segments(9) == 1, "rounds of the value pass");
+  auto with_own = [&](auto&& f) {
+    if (own_v == 1) {
+      if (nst >= 8) f(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
+      else if (nst == 4) f(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+      else f(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+    } else if (own_v == 2) {
+      f(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+    }
+    if constexpr (MAX_RT >= 3)
+      if (own_v == 3) f(std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{});
+    if constexpr (MAX_RT >= 4)
+      if (own_v == 4) f(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
   };
 
-  // ---- the item's 64 query rows -> LDS (in the weight tile's area, idle until
-  // the first tile).  Row-major [column][D]; the 16-byte chunk j of column c is
-  // stored at chunk position j ^ (c % kRowChunks), so the projection's operand
-  // reads (same chunk, 32 columns) hit distinct banks.  Columns past the tile's
+  // ---- the item's 64 query rows (qv, loaded during the previous item) -> LDS
+  // (in the weight tile's area, idle until the first tile).  Row-major
+  // [column][D]; the 16-byte chunk j of column c is stored at chunk position
+  // j ^ (c % kRowChunks), so the projection's operand reads (same chunk, 32
+  // columns) hit distinct banks.  Columns past the tile's
   // last one re-read the last column's query and count as its head (their
   // results are never stored).
-  constexpr int kRowChunks = D / 8;              // 16-byte chunks per query row
-  constexpr int kRowsPerLoad = 64 / kRowChunks;  // rows per 1 KiB load
-  const __bf16* qimg = wl;
+  constexpr int kRowChunks = D / 8;  // 16-byte chunks per query row
+  constexpr int kQLoads = query_loads<D>();
+  __bf16* qimg = wl;
+  // steps KD .. of an R^K rank tile (kPair: in the slots' second fragments)
+  constexpr bool kMoreRk = !kPair && NK > KD;
+  bf16x8 rk_more[kMoreRk ? KD : 1];
   {
-    const uint32_t qimg_lds = __builtin_amdgcn_readfirstlane(lds_addr(qimg));
-    const int cl_lane = lane / kRowChunks, pos = lane % kRowChunks;
-    for (int f = wave; f < kCols / kRowsPerLoad; f += kWaves) {
-      const int cl = kRowsPerLoad * f + cl_lane;
-      const uint16_t* src = a.q + query_row(c0 + min(cl, cn - 1), N_g, G, a.H_q) * D + 8 * (pos ^ (cl % kRowChunks));
-      lds_dma16(src, qimg_lds + f * 1024);
+#pragma unroll
+    for (int u = 0; u < kQLoads; ++u) {
+      const unsigned x = opaque(tid) + u * kThreads, cl = x / kRowChunks, j = x % kRowChunks;
+      *reinterpret_cast<bf16x8*>(qimg + cl * D + 8 * (j ^ (cl % kRowChunks))) = qv[u];
     }
-    if (wave == 0) rd.derive(lane);  // the runs of the block item two ahead, while the rows load
-    wait_vmcnt<0>();
+    if constexpr (I8) {
+      // the previous item could not load this one's first K run (its element size may differ)
+      static_for<0, KD, 1>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if (n_rk > 0) {
+          fs.ks[i][0] = ldf(rkp, i * kFragBytes);
+          if constexpr (kPair) fs.ks[i][1] = ldf(rkp, (i + KD) * kFragBytes, -(int)(NK > KD));
+        } else {
+          fs.ks[i][0] = ldp(pk_first.p, pk_first.off(i));
+          if constexpr (kPair) fs.ks[i][1] = ldp(pk_first.p, pk_first.off(i) + pk_first.delta, pk_first.wanted2);
+        }
+      });
+    }
+    // the rest of the first R^K rank tile, then the first tile's P^V
+    if constexpr (kMoreRk)
+      static_for<0, KD, 1>([&](auto i) { rk_more[decltype(i)::value] = ldf(rkp, (i + KD) * kFragBytes, mask_lt(0, n_rk)); });
+    static_for<0, VD, 1>([&](auto x) { forget(fs.vs[decltype(x)::value]); });
+    with_own([&](auto own_c, auto cs_c) {
+      constexpr int n = decltype(own_c)::value * decltype(cs_c)::value;
+      static_for<0, (n < VD ? n : VD), 1>([&](auto x) { fs.vs[decltype(x)::value] = ldp(pvp, x * kPBytes); });
+    });
+    if (wave == 0) rd.derive(lane);  // the runs of the block item two ahead
     lds_barrier();
   }
 
+  auto load_pk_first = [&]() {
+    static_for<0, KD, 1>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      fs.ks[i][0] = ldp(pk_first.p, pk_first.off(i));
+      if constexpr (kPair) fs.ks[i][1] = ldp(pk_first.p, pk_first.off(i) + pk_first.delta, pk_first.wanted2);
+    });
+  };
   // ---- projection: Qt[rank][col] (stored [col][rank]), once per KV head of
   // the tile; each column stores its own head's result.  Dense items: Qt is
   // the query itself times the sign of the scale, as fp16 (exact for the
@@ -724,8 +778,9 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       float acc[kGemvCols];
 #pragma unroll
       for (int cl = 0; cl < kGemvCols; ++cl) acc[cl] = 0.f;
+      const unsigned char* rp = rkp + ((int64_t)hh * nrt_k * NK + (x - hh * own_k) * NK) * kFragBytes;
       for (int k = 0; k < NK; ++k) {
-        const bf16x8 af = take();
+        const bf16x8 af = ldf(rp, k * kFragBytes);
         float rf[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) rf[e] = (float)af[e];
@@ -746,7 +801,9 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       if (hh == 0)
         for (int cl = cn + lhi; cl < kCols; cl += 2) qt[cl * qsd + 32 * rt + lrow] = (__bf16)0.f;
     }
+    load_pk_first();
   } else if (own_k > 0) {
+    const int ln = opaque(lane), lrow = ln & 31, lhi = ln >> 5;
     bf16x8 qf[NK][2];
 #pragma unroll
     for (int ch = 0; ch < 2; ++ch)
@@ -754,20 +811,34 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       for (int k = 0; k < NK; ++k)
         qf[k][ch] = ld_bf16x8(qimg + (32 * ch + lrow) * D + 8 * ((2 * k + lhi) ^ (lrow % kRowChunks)));
     // KV head (relative to g0) of this lane's two columns 32 ch + lrow
-    const int hq0 = (c0 + min(lrow, cn - 1)) / N_g - g0;
-    const int hq1 = (c0 + min(32 + lrow, cn - 1)) / N_g - g0;
-    for (int x = 0; x < nh * own_k; ++x) {
-      const int hh = x / own_k, rt = wave + kWaves * (x - hh * own_k);
-      f32x16 acc0 = {}, acc1 = {};
-      bf16x8 af = take();
-#pragma unroll
-      for (int k = 0; k < NK; ++k) {
-        bf16x8 an = af;
-        if (k + 1 < NK) an = take();
-        acc0 = mfma32(af, qf[k][0], acc0);
-        acc1 = mfma32(af, qf[k][1], acc1);
-        af = an;
-      }
+    const int hq0 = div_by(c0 + min(lrow, cn - 1), N_g, a.N_g_inv) - g0;
+    const int hq1 = div_by(c0 + min(32 + lrow, cn - 1), N_g, a.N_g_inv) - g0;
+    const int nx = nh * own_k;
+    for (int x = 0; x < nx; ++x) {
+      const int hh = x / own_k, j = x - hh * own_k, rt = wave + kWaves * j;
+      // each step's slot is reloaded with the same step of the next rank tile (the
+      // next head's run starts nrt_k NK fragments on; past the last, P^K)
+      const unsigned char* after = rkp + (j + 1 < own_k ? (int64_t)hh * nrt_k + j + 1 : (int64_t)(hh + 1) * nrt_k) * NK * kFragBytes;
+      const bool to_pk = !I8 && x + 1 == nx;
+      f32x16 acc0 = zero16(), acc1 = zero16();
+      static_for<0, NK, 1>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        if constexpr (k >= KD && !kPair) {
+          acc0 = mfma32(rk_more[k - KD], qf[k][0], acc0);
+          acc1 = mfma32(rk_more[k - KD], qf[k][1], acc1);
+          rk_more[k - KD] = ldf(after, k * kFragBytes, mask_lt(x + 1, nx));
+        } else {
+          constexpr int i = k % KD, u = k / KD;
+          acc0 = mfma32(fs.ks[i][u], qf[k][0], acc0);
+          acc1 = mfma32(fs.ks[i][u], qf[k][1], acc1);
+          const int pk_off = pk_first.off(i) + (u ? pk_first.delta : 0), pk_wanted = u ? pk_first.wanted2 : -1;
+          fs.ks[i][u] = ldf(to_pk ? pk_first.p : after, to_pk ? pk_off : k * kFragBytes,
+                            to_pk ? pk_wanted : mask_lt(x + 1, nx));
+          // one round of R^K: the second fragments are P^K's alone
+          if constexpr (kPair && NK == KD)
+            fs.ks[i][1] = ldf(pk_first.p, pk_first.off(i) + pk_first.delta, to_pk ? pk_first.wanted2 : 0);
+        }
+      });
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj) {
         bf16x4 v0, v1;
@@ -781,280 +852,331 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
         if (hq1 == hh) *reinterpret_cast<bf16x4*>(qt + (32 + lrow) * qsd + r) = v1;
       }
     }
+    if constexpr (I8) load_pk_first();
   }
   lds_barrier();
 
-  // ---- scores, online softmax, latent V ----
-  f32x16 oacc[MAX_RT][2];
-#pragma unroll
-  for (int r = 0; r < MAX_RT; ++r) oacc[r][0] = oacc[r][1] = f32x16{};
+  // ---- scores, online softmax, latent V: the tile loop, then the value pass's
+  // result into LDS.  One instance per number of rank tiles a wave owns in the
+  // value pass, and one for dense items, so that each keeps its own accumulators
+  // and nothing else in registers ----
   float m_run[2] = {-INFINITY, -INFINITY};
   float l_run[2] = {0.f, 0.f};
-  // factor (> 0) from the MFMA's raw scores to scores in log2 units: the
-  // magnitude of the scale for dense items, 1 otherwise (the projection
-  // carries it); applied in the column maximum and the weights' exponent
-  const float sscale = dense && a.qscale != 0.f ? fabsf(a.qscale) : 1.f;
-  const __bf16* qr0 = qt + lrow * qsd + 8 * lhi;
-  const __bf16* qr1 = qt + (32 + lrow) * qsd + 8 * lhi;
-  // weight operand rows of the wave's segment (relative step st at 16 st)
-  const __bf16* wr0 = wl + lrow * kWS + 8 * lhi + 16 * nst * sg;
-  const __bf16* wr1 = wl + (32 + lrow) * kWS + 8 * lhi + 16 * nst * sg;
+  float* lred = reinterpret_cast<float*>(smem + a.work_bytes) - kWaves * kCols;  // [kWaves][kCols]
+  // up-projection: a wave takes two 16-dim slices of the output for a half
+  // (d = 128) or a quarter (d = 64) of the columns, so that each latent operand
+  // read from LDS feeds two MFMAs; rounds of kRvSteps 32-rank steps
+  constexpr int NDS = D / 16, kRvSteps = 4;
+  // (a tile of at most 32 columns, in its first half: one slice per wave, and the
+  // second fragment of a slot is the same slice kRvSteps steps on)
+  const bool narrow = cn <= 32;
+  const int ds0 = narrow ? wave % NDS : 2 * (wave % (NDS / 2));  // the first slice
+  const int nk_v = bm.rv_pad >> 5;
+  const unsigned char* rvp = data + rv_frag(bm, D, g0, ds0, 0) * kFragBytes;
+  bf16x8 rv[kRvSteps][2];
+  auto tiles = [&](auto own_c, auto cs_c, auto dense_c) {
+    constexpr int OWN = decltype(own_c)::value, CS = decltype(cs_c)::value;
+    constexpr bool DENSE = decltype(dense_c)::value;
+    f32x16 oacc[OWN > 0 ? OWN : 1][2];
+#pragma unroll
+    for (int r = 0; r < OWN; ++r) oacc[r][0] = oacc[r][1] = zero16();
+    // factor (> 0) from the MFMA's raw scores to scores in log2 units: the
+    // magnitude of the scale for dense items, 1 otherwise (the projection
+    // carries it); applied in the column maximum and the weights' exponent
+    const float sscale = DENSE && a.qscale != 0.f ? fabsf(a.qscale) : 1.f;
 
-  for (int tt = 0; tt < ntiles; ++tt) {
-    const int tw = (tile0 + tt) * kTile + wave * kTokWave;
-    f32x16 s0 = {}, s1 = {};
-    // operands of rank step k: ak (P^K sub-tile, or rebuilt keys), b0/b1 (Qt
-    // column tiles); nks is even (ranks are padded to 32), so the loop runs over
-    // step pairs; dense items multiply fp16 operands
-    auto scores = [&](auto mma) {
-      bf16x8 ak = take_p();
-      bf16x8 b0 = ld_bf16x8(qr0), b1 = ld_bf16x8(qr1);
-      for (int k = 0; k < nks; k += 2) {
-        const bf16x8 ck = take_p();
-        const bf16x8 d0 = ld_bf16x8(qr0 + 16 * (k + 1));
-        const bf16x8 d1 = ld_bf16x8(qr1 + 16 * (k + 1));
-        s0 = mma(ak, b0, s0);
-        s1 = mma(ak, b1, s1);
-        if (k + 2 < nks) {
-          ak = take_p();
-          b0 = ld_bf16x8(qr0 + 16 * (k + 2));
-          b1 = ld_bf16x8(qr1 + 16 * (k + 2));
-        }
-        s0 = mma(ck, d0, s0);
-        s1 = mma(ck, d1, s1);
+    // one step of NT tiles from tile tt on
+    auto take = [&](int tt, auto nt_c) {
+      constexpr int NT = decltype(nt_c)::value;
+      const int after = tt + NT;  // the next step's first tile
+      float scale_unit[NT];       // INT8: this lane's entry of the wave's scale unit of each tile
+      if constexpr (I8) {
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+          scale_unit[u] = reinterpret_cast<const float*>(scp + (int64_t)(tt + u) * kWaves * kScaleUnitBytes)[lane];
       }
-    };
-    if constexpr (I8) {
-      scores(mfma32);
-    } else {
-      if (dense) scores(mfma32_f16);
-      else scores(mfma32);
-    }
-    f32x16 sc[2] = {s0, s1};
-    // INT8 P factors: the scores of int8 codes times each token's K scale; the
-    // V scales fold into the weights below (lane: tokens 8 j + 4 lhi + u of the
-    // wave's 32, j, u = 0..3)
-    float vsc[16];
-    if constexpr (I8) {
-      const float* su = fr.take_scales();
+      // rank step k (P^K sub-tiles, or rebuilt keys) times the two column halves
+      // of Qt; dense items multiply fp16 operands.  The next K run: the next
+      // tiles', then the next item's first (INT8: loaded by that item)
+      f32x16 sc[NT][2];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float4 k4 = *reinterpret_cast<const float4*>(su + 8 * j + 4 * lhi);
-        const float4 v4 = *reinterpret_cast<const float4*>(su + 32 + 8 * j + 4 * lhi);
-        const float kk[4] = {k4.x, k4.y, k4.z, k4.w}, vv[4] = {v4.x, v4.y, v4.z, v4.w};
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          sc[0][4 * j + u] *= kk[u];
-          sc[1][4 * j + u] *= kk[u];
-          vsc[4 * j + u] = vv[u];
+      for (int u = 0; u < NT; ++u) sc[u][0] = sc[u][1] = zero16();
+      {
+        const int ln = opaque(lane);
+        const __bf16* qr0 = qt + (ln & 31) * qsd + 8 * (ln >> 5);
+        const __bf16* qr1 = qr0 + 32 * qsd;
+        const unsigned char* kb = pkp + (int64_t)tt * nks * kPBytes;
+        RunStart<KD, kPBytes> kn(kb + (int64_t)NT * nks * kPBytes, nks, nks * kPBytes, mask_lt(after + 1, ntiles));
+        if (after >= ntiles) {
+          kn.wanted = kn.wanted2 = 0;
+          if constexpr (!I8)
+            if (next_item) kn = item_first_run<D, MAX_RT>(next_item, wave, data + (int64_t)rl.next_first() * kPBytes);
         }
+        auto use = [&](int f, auto slot) {
+          constexpr int i = decltype(slot)::value;
+          const bf16x8 b0 = ld_bf16x8(qr0 + 16 * f + 16 * i), b1 = ld_bf16x8(qr1 + 16 * f + 16 * i);
+          static_for<0, NT, 1>([&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            const bf16x8 ak = use_p(fs.ks[i][u]);
+            sc[u][0] = DENSE ? mfma32_f16(ak, b0, sc[u][0]) : mfma32(ak, b0, sc[u][0]);
+            sc[u][1] = DENSE ? mfma32_f16(ak, b1, sc[u][1]) : mfma32(ak, b1, sc[u][1]);
+          });
+        };
+        consume_run(kb, nks, nks * kPBytes, NT == 2 ? -1 : 0, kn, use,
+                    [&](auto slot, const unsigned char* q, int off, int wanted, int delta, int wanted2) {
+                      constexpr int i = decltype(slot)::value;
+                      fs.ks[i][0] = ldp(q, off, wanted);
+                      if constexpr (kPair) fs.ks[i][1] = ldp(q, off + delta, wanted2);
+                    });
       }
-    }
-    // mask tokens past the end of the block (only the block's last tile can
-    // hold any; the test is wave-uniform), and for a prefill chunk's shared
-    // tail the tokens past each column's causal limit; wave-local column max
-    float mx[2] = {-INFINITY, -INFINITY};
-    if (tw + kTokWave > T || (causal && tw + kTokWave > lim_min)) {
+      const int ln = opaque(lane), lrow = ln & 31, lhi = ln >> 5;
+      // INT8 P factors: the scores of int8 codes times each token's K scale (lane:
+      // tokens 8 j + 4 lhi + v of the wave's 32, j, v = 0..3); the V scales fold
+      // into the weights below.  The units are spread through LDS: without pairs
+      // through the wave's own maxima row, which nobody reads before the maxima
+      // below are in it
+      float vsc[16];
+      if constexpr (I8) {
+        float* su = kPair ? units : red + wave * kCols;
 #pragma unroll
-      for (int ch = 0; ch < 2; ++ch)
+        for (int u = 0; u < NT; ++u) {
+          su[64 * u + ln] = scale_unit[u];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int tok = tw + 8 * (v >> 2) + 4 * lhi + (v & 3);
-          if (tok >= T || tok >= lim[ch]) sc[ch][v] = -INFINITY;
-        }
-    }
+          for (int j = 0; j < 4; ++j) {
+            const float4 k4 = *reinterpret_cast<const float4*>(su + 64 * u + 8 * j + 4 * lhi);
+            const float kk[4] = {k4.x, k4.y, k4.z, k4.w};
+            if constexpr (!kPair) {
+              const float4 v4 = *reinterpret_cast<const float4*>(su + 32 + 8 * j + 4 * lhi);
+              vsc[4 * j] = v4.x, vsc[4 * j + 1] = v4.y, vsc[4 * j + 2] = v4.z, vsc[4 * j + 3] = v4.w;
+            }
 #pragma unroll
-    for (int ch = 0; ch < 2; ++ch)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) mx[ch] = fmaxf(mx[ch], sc[ch][v]);
-#pragma unroll
-    for (int ch = 0; ch < 2; ++ch) {
-      mx[ch] = fmaxf(mx[ch], __shfl_xor(mx[ch], 32)) * sscale;
-      red[wave * kCols + 32 * ch + lrow] = mx[ch];  // both lane halves hold the same value
-    }
-    lds_barrier();
-    float alpha[2];
-#pragma unroll
-    for (int ch = 0; ch < 2; ++ch) {
-      float tm = red[32 * ch + lrow];
-#pragma unroll
-      for (int w = 1; w < kWaves; ++w) tm = fmaxf(tm, red[w * kCols + 32 * ch + lrow]);
-      const float mn = fmaxf(m_run[ch], tm);
-      // a column with no key so far (a causal column before its first token)
-      // keeps m = -inf and zero weights
-      alpha[ch] = mn == -INFINITY ? 1.f : fast_exp2(m_run[ch] - mn);
-      m_run[ch] = mn;
-    }
-    // weights W = 2^(s - m) (bf16) in registers, then to LDS as [col][token]
-    bf16x4 wv[2][4];
-#pragma unroll
-    for (int ch = 0; ch < 2; ++ch) {
-      float lsum = 0.f;
-      const float mref = m_run[ch] == -INFINITY ? 0.f : m_run[ch];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float w = fast_exp2(fmaf(sc[ch][4 * j + u], sscale, -mref));
-          lsum += w;
-          if constexpr (I8) wv[ch][j][u] = (__bf16)(w * vsc[4 * j + u]);
-          else wv[ch][j][u] = (__bf16)w;
-        }
-      l_run[ch] = l_run[ch] * alpha[ch] + lsum;
-    }
-    auto write_w = [&]() {
-      const int tcol = (WH ? (wave & 3) : wave) * kTokWave;  // the wave's tokens in the (half) tile
-#pragma unroll
-      for (int ch = 0; ch < 2; ++ch)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          *reinterpret_cast<bf16x4*>(wl + (32 * ch + lrow) * kWS + tcol + 8 * j + 4 * lhi) = wv[ch][j];
-    };
-    // latent V over the wave's relative steps [lo, hi) (even bounds), weights
-    // of relative step st at w0p / w1p + 16 st
-    auto vpass = [&](int lo, int hi, const __bf16* w0p, const __bf16* w1p) {
-      if (own_v <= 0 || lo >= hi) return;
-      // operands of 16-token step st: w0/w1 (weight column tiles), pa[r] (P^V rank
-      // tiles); the loop runs over step pairs
-      bf16x8 pa[MAX_RT], pc[MAX_RT];
-      bf16x8 w0 = ld_bf16x8(w0p + 16 * lo), w1 = ld_bf16x8(w1p + 16 * lo);
-#pragma unroll
-      for (int r = 0; r < MAX_RT; ++r)
-        if (r < own_v) pa[r] = take_p();
-      for (int st = lo; st < hi; st += 2) {
-        const bf16x8 x0 = ld_bf16x8(w0p + 16 * (st + 1));
-        const bf16x8 x1 = ld_bf16x8(w1p + 16 * (st + 1));
-#pragma unroll
-        for (int r = 0; r < MAX_RT; ++r)
-          if (r < own_v) pc[r] = take_p();
-#pragma unroll
-        for (int r = 0; r < MAX_RT; ++r)
-          if (r < own_v) {
-            oacc[r][0] = mfma32(pa[r], w0, oacc[r][0]);
-            oacc[r][1] = mfma32(pa[r], w1, oacc[r][1]);
+            for (int v = 0; v < 4; ++v) {
+              sc[u][0][4 * j + v] *= kk[v];
+              sc[u][1][4 * j + v] *= kk[v];
+            }
           }
-        if (st + 2 < hi) {
-          w0 = ld_bf16x8(w0p + 16 * (st + 2));
-          w1 = ld_bf16x8(w1p + 16 * (st + 2));
+        }
+      }
+      // mask tokens past the end of the block (only the block's last tile can
+      // hold any; the test is wave-uniform), and for a prefill chunk's shared
+      // tail the tokens past each column's causal limit; wave-local column max
+      float mx[2] = {-INFINITY, -INFINITY};
 #pragma unroll
-          for (int r = 0; r < MAX_RT; ++r)
-            if (r < own_v) pa[r] = take_p();
+      for (int u = 0; u < NT; ++u) {
+        const int tw = (tile0 + tt + u) * kTile + wave * kTokWave;
+        if (tw + kTokWave > T || (DENSE && causal && tw + kTokWave > lim_min)) {
+#pragma unroll
+          for (int ch = 0; ch < 2; ++ch)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              const int tok = tw + 8 * (v >> 2) + 4 * lhi + (v & 3);
+              if (tok >= T || (DENSE && tok >= lim[ch])) sc[u][ch][v] = -INFINITY;
+            }
         }
 #pragma unroll
-        for (int r = 0; r < MAX_RT; ++r)
-          if (r < own_v) {
-            oacc[r][0] = mfma32(pc[r], x0, oacc[r][0]);
-            oacc[r][1] = mfma32(pc[r], x1, oacc[r][1]);
-          }
-      }
-    };
-    auto rescale = [&]() {
-      // rescale the latent accumulators to the new running maximum; skipped on
-      // the first tile (they are zero) and when no column's maximum moved
-      if (tt > 0 && own_v > 0 && __any(alpha[0] != 1.f || alpha[1] != 1.f)) {
+        for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
-        for (int r = 0; r < MAX_RT; ++r)
-          if (r < own_v) {
+          for (int v = 0; v < 16; ++v) mx[ch] = fmaxf(mx[ch], sc[u][ch][v]);
+      }
+#pragma unroll
+      for (int ch = 0; ch < 2; ++ch) {
+        mx[ch] = fmaxf(mx[ch], __shfl_xor(mx[ch], 32)) * sscale;
+        red[wave * kCols + 32 * ch + lrow] = mx[ch];  // both lane halves hold the same value
+      }
+      lds_barrier();
+      // The gang's workgroups read the same P at the same time, so what they have
+      // in flight from HBM together is only one workgroup's: each fetches its share
+      // of the wave's coming fragments (this tile's P^V, then the next one's P^K,
+      // in 64 lines of 128 bytes) into the XCD's L2.  Issued here no younger load
+      // is needed before the value pass' second round, so the fetch, whose value is
+      // never used, holds nobody up (loads return in order).  Not with pairs: their
+      // steps leave no register for it
+      uint32_t touched[kTouches > 0 ? kTouches : 1];
+      if constexpr (kTouches > 0) {
+        const int lane128 = 128 * opaque(lane);
+        const int v_lines = OWN > 0 ? nst * OWN * (kPBytes / 128) : 0, v_chunks = (v_lines + 63) >> 6;
+        const int k_lines = after < ntiles ? nks * (kPBytes / 128) : 0;
+#pragma unroll
+        for (int l = 0; l < kTouches; ++l) {
+          const int c = gang_at + l * a.gang;
+          const bool k_part = c >= v_chunks;
+          const int at = (k_part ? c - v_chunks : c) * 8192;
+          const unsigned char* base = k_part ? pkp + (int64_t)after * nks * kPBytes : pvp + (int64_t)tt * 16 * OWN * kPBytes;
+          // an empty buffer past the part's end, and for a gang of one
+          const int bytes = a.gang > 1 ? max(0, min(8192, (k_part ? k_lines : v_lines) * 128 - at)) : 0;
+          const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+              const_cast<unsigned char*>(base) + at, 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+          touched[l] = __builtin_amdgcn_raw_buffer_load_b32(r, lane128, 0, 0);
+        }
+      }
+      float alpha[2];
+#pragma unroll
+      for (int ch = 0; ch < 2; ++ch) {
+        float tm = red[32 * ch + lrow];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) tm = fmaxf(tm, red[w * kCols + 32 * ch + lrow]);
+        const float mn = fmaxf(m_run[ch], tm);
+        // a column with no key so far (a causal column before its first token)
+        // keeps m = -inf and zero weights
+        alpha[ch] = mn == -INFINITY ? 1.f : fast_exp2(m_run[ch] - mn);
+        m_run[ch] = mn;
+      }
+      // weights W = 2^(s - m) (bf16) to LDS as [col][token]
+#pragma unroll
+      for (int ch = 0; ch < 2; ++ch) {
+        float lsum = 0.f;
+        const float mref = m_run[ch] == -INFINITY ? 0.f : m_run[ch];
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if constexpr (I8 && kPair) {
+              const float4 v4 = *reinterpret_cast<const float4*>(units + 64 * u + 32 + 8 * j + 4 * lhi);
+              vsc[4 * j] = v4.x, vsc[4 * j + 1] = v4.y, vsc[4 * j + 2] = v4.z, vsc[4 * j + 3] = v4.w;
+            }
+            bf16x4 wv;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const float w = fast_exp2(fmaf(sc[u][ch][4 * j + v], sscale, -mref));
+              lsum += w;
+              if constexpr (I8) wv[v] = (__bf16)(w * vsc[4 * j + v]);
+              else wv[v] = (__bf16)w;
+            }
+            *reinterpret_cast<bf16x4*>(wl + (32 * ch + lrow) * kWS + u * kTile + wave * kTokWave + 8 * j + 4 * lhi) = wv;
+          }
+        l_run[ch] = l_run[ch] * alpha[ch] + lsum;
+        // summed here: left to itself the compiler keeps all the weights to sum them later
+        asm volatile("" : "+v"(l_run[ch]));
+      }
+      if constexpr (OWN > 0) {
+        // latent V over the wave's token segment of each tile: 16-token step st is
+        // slots st % CS (its OWN rank tiles), reloaded a round ahead: this tile's,
+        // then the next tile's; the slots past VD hold a step's fragments only
+        // here (the scores' registers are free)
+        constexpr int NF = CS * OWN;  // fragments in a round
+        bf16x8 vx[NF > VD ? NF - VD : 1];
+        const unsigned char* vb = pvp + (int64_t)tt * 16 * OWN * kPBytes;
+        static_for<VD, NF, 1>([&](auto x) { vx[decltype(x)::value - VD] = ldp(vb, x * kPBytes); });
+        lds_barrier();
+        // rescale the latent accumulators to the new running maximum; skipped on
+        // the first tiles (they are zero) and when no column's maximum moved
+        if (tt > 0 && __any(alpha[0] != 1.f || alpha[1] != 1.f)) {
+#pragma unroll
+          for (int r = 0; r < OWN; ++r) {
             oacc[r][0] *= alpha[0];
             oacc[r][1] *= alpha[1];
           }
+        }
+        const int steps = OWN > 2 ? 16 : nst;  // a whole number of rounds
+#pragma clang loop unroll(disable)
+        for (int u = 0; u < NT; ++u) {
+          // weight operand rows of the wave's segment (relative step st at 16 st)
+          const __bf16* wr0 = wl + lrow * kWS + 8 * lhi + u * kTile + 16 * nst * sg;
+          const __bf16* wr1 = wr0 + 32 * kWS;
+          const unsigned char* vu = vb + u * 16 * OWN * kPBytes;
+#pragma clang loop unroll(disable)
+          for (int st = 0; st < steps; st += CS) {
+            const int in_step = mask_lt(st + CS, steps) | mask_lt(u + 1, NT);
+            const int wanted = in_step | mask_lt(after, ntiles);
+            const int on = (st + CS >= steps ? 16 : st + CS) * OWN * kPBytes;
+            static_for<0, CS, 1>([&](auto ic) {
+              constexpr int i = decltype(ic)::value;
+              const bf16x8 w0 = ld_bf16x8(wr0 + 16 * st + 16 * i), w1 = ld_bf16x8(wr1 + 16 * st + 16 * i);
+              static_for<0, OWN, 1>([&](auto rc) {
+                constexpr int r = decltype(rc)::value, x = i * OWN + r;
+                bf16x8& slot = [&]() -> bf16x8& {
+                  if constexpr (x < VD) return fs.vs[x];
+                  else return vx[x - VD];
+                }();
+                const bf16x8 pa = use_p(slot);
+                oacc[r][0] = mfma32(pa, w0, oacc[r][0]);
+                oacc[r][1] = mfma32(pa, w1, oacc[r][1]);
+                slot = ldp(vu, on + x * kPBytes, x < VD ? wanted : in_step);
+              });
+            });
+          }
+        }
+      } else {
+        lds_barrier();
       }
+#pragma unroll
+      for (int l = 0; l < kTouches; ++l) asm volatile("" ::"v"(touched[l]));
     };
-    if constexpr (!WH) {
-      write_w();
-      lds_barrier();
-      rescale();
-      vpass(0, nst, wr0, wr1);
-    } else {
-      // half h holds the tokens of waves 4h .. 4h+3, i.e. tile steps [8h, 8h + 8);
-      // the wave's segment covers tile steps [nst sg, nst sg + nst)
-      if (wave < 4) write_w();
-      lds_barrier();
-      rescale();
-      vpass(0, min(nst, 8 - nst * sg), wr0, wr1);
-      lds_barrier();  // every wave is done with the first half's weights
-      if (wave >= 4) write_w();
-      lds_barrier();
-      vpass(max(0, 8 - nst * sg), nst, wr0 - 16 * 8, wr1 - 16 * 8);
-    }
-  }
+    int tt = 0;
+    if constexpr (kPair)
+      for (; tt + 1 < ntiles; tt += 2) take(tt, std::integral_constant<int, 2>{});
+    for (; tt < ntiles; ++tt) take(tt, std::integral_constant<int, 1>{});
 
-  // ---- up-projection through R^V and the partial (m, l, o) ----
+    // the up-projection's first R^V steps load while the partials are combined
+    if constexpr (!DENSE)
+      static_for<0, kRvSteps, 1>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        rv[i][0] = ldf(rvp, i * kFragBytes, mask_lt(i, nk_v));
+        rv[i][1] = ldf(rvp, ((narrow ? kRvSteps : nk_v) + i) * kFragBytes, mask_lt(narrow ? i + kRvSteps : i, nk_v));
+      });
+    const int ln = opaque(lane), lrow = ln & 31, lhi = ln >> 5;
 #pragma unroll
-  for (int ch = 0; ch < 2; ++ch) l_run[ch] += __shfl_xor(l_run[ch], 32);
-  lds_barrier();  // every wave is done with qt / wl
-  float* lred = reinterpret_cast<float*>(smem + a.ring_offset) - kWaves * kCols;  // [kWaves][kCols]
-  lred[wave * kCols + lrow] = l_run[0];  // both lane halves hold the sums
-  lred[wave * kCols + 32 + lrow] = l_run[1];
-  // combine the token segments' latent partials (pairwise rounds through LDS,
-  // fp32): the waves of segments [h, 2h) hand theirs to segments [0, h)
-  if (nseg > 1) {
-    float* segbuf = reinterpret_cast<float*>(smem);  // [slot][owned tile][ch][16][64 lanes]
-    const int own_max = (nrt_v + ng - 1) / ng;        // slot size: the largest rank group's tiles
-    for (int h = nseg / 2; h >= 1; h /= 2) {
-      if (sg >= h && sg < 2 * h) {
-        float* dst = segbuf + (int64_t)((sg - h) * ng + rg) * own_max * 2 * 16 * 64 + lane;
+    for (int ch = 0; ch < 2; ++ch) l_run[ch] += __shfl_xor(l_run[ch], 32);
+    lds_barrier();  // every wave is done with qt / wl
+    lred[wave * kCols + lrow] = l_run[0];  // both lane halves hold the sums
+    lred[wave * kCols + 32 + lrow] = l_run[1];
+    // combine the token segments' latent partials (pairwise rounds through LDS,
+    // fp32): the waves of segments [h, 2h) hand theirs to segments [0, h)
+    if (nseg > 1) {
+      float4* segbuf = reinterpret_cast<float4*>(smem);  // [slot][owned tile][ch][4][64 lanes]
+      const int own_max = (nrt_v + ng - 1) / ng;        // slot size: the largest rank group's tiles
+      for (int h = nseg / 2; h >= 1; h /= 2) {
+        if (sg >= h && sg < 2 * h) {
+          float4* dst = segbuf + ((sg - h) * ng + rg) * own_max * 2 * 4 * 64 + ln;
 #pragma unroll
-        for (int r = 0; r < MAX_RT; ++r)
-          if (r < own_v)
-#pragma unroll
-            for (int ch = 0; ch < 2; ++ch)
-#pragma unroll
-              for (int v = 0; v < 16; ++v) dst[((r * 2 + ch) * 16 + v) * 64] = oacc[r][ch][v];
-      }
-      lds_barrier();
-      if (sg < h) {
-        const float* src = segbuf + (int64_t)(sg * ng + rg) * own_max * 2 * 16 * 64 + lane;
-#pragma unroll
-        for (int r = 0; r < MAX_RT; ++r)
-          if (r < own_v)
+          for (int r = 0; r < OWN; ++r)
 #pragma unroll
             for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
-              for (int v = 0; v < 16; ++v) oacc[r][ch][v] += src[((r * 2 + ch) * 16 + v) * 64];
+              for (int v = 0; v < 4; ++v)
+                dst[((r * 2 + ch) * 4 + v) * 64] = make_float4(oacc[r][ch][4 * v], oacc[r][ch][4 * v + 1],
+                                                               oacc[r][ch][4 * v + 2], oacc[r][ch][4 * v + 3]);
+        }
+        lds_barrier();
+        if (sg < h) {
+          const float4* src = segbuf + (sg * ng + rg) * own_max * 2 * 4 * 64 + ln;
+#pragma unroll
+          for (int r = 0; r < OWN; ++r)
+#pragma unroll
+            for (int ch = 0; ch < 2; ++ch)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                const float4 x = src[((r * 2 + ch) * 4 + v) * 64];
+                oacc[r][ch][4 * v] += x.x;
+                oacc[r][ch][4 * v + 1] += x.y;
+                oacc[r][ch][4 * v + 2] += x.z;
+                oacc[r][ch][4 * v + 3] += x.w;
+              }
+        }
+        lds_barrier();
       }
-      lds_barrier();
     }
-  }
-  constexpr int NDS = D / 16;              // 16-dim slices
-  constexpr int NCB = up_col_blocks<D>();  // 16-column blocks per wave
-  const int ds = wave % NDS, cb0 = (wave / NDS) * NCB;
-  f32x4 uacc[NCB];
-  if (dense) {
-    // the value pass already produced the output: its accumulators (fp32,
-    // [col][dim]) through LDS into the up-projection's lane layout
-    float* of = reinterpret_cast<float*>(smem);
-    constexpr int ofs = D + 4;
     if (sg == 0) {
+      if constexpr (DENSE) {
+        // the value pass already produced the output: its accumulators (fp32,
+        // [col][dim]) through LDS into the up-projection's lane layout
+        float* of = reinterpret_cast<float*>(smem);
+        constexpr int ofs = D + 4;
 #pragma unroll
-      for (int r = 0; r < MAX_RT; ++r)
-        if (r < own_v) {
-          const int rt = rg + ng * r;
+        for (int r = 0; r < OWN; ++r)
 #pragma unroll
           for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
-              *reinterpret_cast<float4*>(of + (32 * ch + lrow) * ofs + 32 * rt + 8 * jj + 4 * lhi) =
+              *reinterpret_cast<float4*>(of + (32 * ch + lrow) * ofs + 32 * (rg + ng * r) + 8 * jj + 4 * lhi) =
                   make_float4(oacc[r][ch][4 * jj], oacc[r][ch][4 * jj + 1], oacc[r][ch][4 * jj + 2],
                               oacc[r][ch][4 * jj + 3]);
-        }
-    }
-    lds_barrier();
+      } else {
+        // the latent accumulator of every rank tile -> LDS as bf16 [col][rank]
+        __bf16* olat = reinterpret_cast<__bf16*>(smem);
+        const int ols = bm.rv_pad + 8;
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-      const float4 v = *reinterpret_cast<const float4*>(of + (16 * (cb0 + cb) + (lane & 15)) * ofs + 16 * ds +
-                                                        4 * (lane >> 4));
-      uacc[cb] = f32x4{v.x, v.y, v.z, v.w};
-    }
-  } else {
-    // the latent accumulator of every rank tile -> LDS as bf16 [col][rank]
-    __bf16* olat = reinterpret_cast<__bf16*>(smem);
-    const int ols = bm.rv_pad + 8;
-    if (sg == 0) {
-#pragma unroll
-      for (int r = 0; r < MAX_RT; ++r)
-        if (r < own_v) {
-          const int rt = rg + ng * r;
+        for (int r = 0; r < OWN; ++r)
 #pragma unroll
           for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
@@ -1062,36 +1184,118 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
               bf16x4 v;
 #pragma unroll
               for (int u = 0; u < 4; ++u) v[u] = (__bf16)oacc[r][ch][4 * jj + u];
-              *reinterpret_cast<bf16x4*>(olat + (32 * ch + lrow) * ols + 32 * rt + 8 * jj + 4 * lhi) = v;
+              *reinterpret_cast<bf16x4*>(olat + (32 * ch + lrow) * ols + 32 * (rg + ng * r) + 8 * jj + 4 * lhi) = v;
             }
-        }
+      }
     }
     lds_barrier();
-    // every wave: output dims [16 ds, 16 ds + 16) of its 16-column blocks, over
-    // all ranks (16x16x32 MFMAs: R^V fragment x latent columns from LDS)
-    {
-      // KV head (relative to g0) of this lane's output columns
-      int hu[NCB];
+  };
+  if (!I8 && dense) {
+    // at rank d every wave owns one rank tile over 8 (d = 128) or 4 (d = 64) steps
+    if constexpr (!I8)
+      tiles(std::integral_constant<int, 1>{}, std::integral_constant<int, D == 128 ? 8 : 4>{}, std::true_type{});
+  } else if (own_v == 0) {
+    tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, std::false_type{});
+  } else {
+    with_own([&](auto own_c, auto cs_c) { tiles(own_c, cs_c, std::false_type{}); });
+  }
+
+  // ---- up-projection through R^V and the partial (m, l, o) ----
+  const int ln = opaque(lane);
+  constexpr int NCB = NDS / 4;               // 16-column blocks per wave
+  const int cb0 = wave / (narrow ? NDS : NDS / 2) * NCB;  // the first of them
+  // this thread's output dims of its columns in the slot
+  int64_t colg[NCB];
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) hu[cb] = (c0 + min(16 * (cb0 + cb) + (lane & 15), cn - 1)) / N_g - g0;
-      const int nk = bm.rv_pad >> 5;
-      const __bf16* ob = olat + (16 * cb0 + (lane & 15)) * ols + 8 * (lane >> 4);
-      for (int hh = 0; hh < nh; ++hh) {
-        f32x4 t[NCB];
+  for (int cb = 0; cb < NCB; ++cb) colg[cb] = query_row(a, c0 + min(16 * (cb0 + cb) + (ln & 15), cn - 1));
+  auto slot_o = [&](int cb, int sl) {
+    return reinterpret_cast<float4*>(a.part_o + (colg[cb] * a.n_slots + slot) * D + 16 * (ds0 + sl) +
+                                     4 * (ln >> 4));
+  };
+  // loads that the end of the item and the next one wait for: the group's
+  // running output, the next item's queries
+  const bool first = (it.flags & kItemFirst) != 0;
+  float4 old[NCB][2];
+  if (!first) {
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) t[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        bf16x8 af = take();
-        for (int k = 0; k < nk; ++k) {
-          bf16x8 an = af;
-          if (k + 1 < nk) an = take();
+    for (int cb = 0; cb < NCB; ++cb) {
+      old[cb][0] = *slot_o(cb, 0);
+      if (!narrow) old[cb][1] = *slot_o(cb, 1);
+    }
+  }
+  if (next_item) {
+    const int nc0 = __builtin_amdgcn_readfirstlane(next_item->req), nf = __builtin_amdgcn_readfirstlane(next_item->flags);
+    load_queries<D>(a, nc0, ((nf >> kItemColsShift) & 63) + 1, tid, qv);
+  } else {
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) t[cb] = mfma16(af, ld_bf16x8(ob + 16 * cb * ols + 32 * k), t[cb]);
-          af = an;
-        }
+    for (int u = 0; u < kQLoads; ++u) forget(qv[u]);
+  }
+  f32x4 uacc[NCB][2];
+  if (dense) {
+    const float* of = reinterpret_cast<const float*>(smem);
+    constexpr int ofs = D + 4;
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-          if (hh == 0 || hu[cb] == hh) uacc[cb] = t[cb];
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+      for (int sl = 0; sl < (narrow ? 1 : 2); ++sl) {
+        const float4 v = *reinterpret_cast<const float4*>(of + (16 * (cb0 + cb) + (ln & 15)) * ofs +
+                                                          16 * (ds0 + sl) + 4 * (ln >> 4));
+        uacc[cb][sl] = f32x4{v.x, v.y, v.z, v.w};
       }
+  } else {
+    // output dims 32 dp .. + 31 of the wave's columns, over all ranks (16x16x32
+    // MFMAs: R^V fragment x latent columns from LDS)
+    const __bf16* olat = reinterpret_cast<const __bf16*>(smem);
+    const int ols = bm.rv_pad + 8;
+    // KV head (relative to g0) of this lane's output columns
+    int hu[NCB];
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) hu[cb] = div_by(c0 + min(16 * (cb0 + cb) + (ln & 15), cn - 1), N_g, a.N_g_inv) - g0;
+    const __bf16* ob = olat + (16 * cb0 + (ln & 15)) * ols + 8 * (ln >> 4);
+    for (int hh = 0; hh < nh; ++hh) {
+      f32x4 t[NCB][2];
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) t[cb][0] = t[cb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      // the head's runs of the two slices, kRvSteps at a time; a slot is reloaded
+      // with the step a round later, or the next head's (NDS nk_v fragments on)
+      const unsigned char* rb = rvp + (int64_t)hh * NDS * nk_v * kFragBytes;
+      const int round = narrow ? 2 * kRvSteps : kRvSteps;
+      for (int k = 0; k < nk_v; k += round) {
+        const bool last = k + round >= nk_v;
+        const unsigned char* q = rb + (int64_t)(last ? NDS * nk_v : k + round) * kFragBytes;
+        const int have = last ? hh + 1 < nh ? nk_v : 0 : nk_v - k - round;  // steps at q
+        static_for<0, kRvSteps, 1>([&](auto ic) {
+          constexpr int i = decltype(ic)::value;
+          bf16x8 b[NCB];  // past the ranks: read, not used
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) b[cb] = ld_bf16x8(ob + 16 * cb * ols + 32 * (k + i));
+          if (k + i < nk_v) {
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) t[cb][0] = mfma16(rv[i][0], b[cb], t[cb][0]);
+            if (!narrow) {
+#pragma unroll
+              for (int cb = 0; cb < NCB; ++cb) t[cb][1] = mfma16(rv[i][1], b[cb], t[cb][1]);
+            }
+          }
+          rv[i][0] = ldf(q, i * kFragBytes, mask_lt(i, have));
+          if (!narrow) rv[i][1] = ldf(q, (nk_v + i) * kFragBytes, mask_lt(i, have));
+        });
+        if (narrow)
+          static_for<0, kRvSteps, 1>([&](auto ic) {
+            constexpr int i = decltype(ic)::value + kRvSteps;
+            bf16x8 b[NCB];
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) b[cb] = ld_bf16x8(ob + 16 * cb * ols + 32 * (k + i));
+            if (k + i < nk_v) {
+#pragma unroll
+              for (int cb = 0; cb < NCB; ++cb) t[cb][0] = mfma16(rv[i - kRvSteps][1], b[cb], t[cb][0]);
+            }
+            rv[i - kRvSteps][1] = ldf(q, i * kFragBytes, mask_lt(i, have));
+          });
+      }
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb)
+        if (hh == 0 || hu[cb] == hh) uacc[cb][0] = t[cb][0], uacc[cb][1] = t[cb][1];
     }
   }  // latent up-projection
   // the item's partial: per-column maximum m_run (score layout), sum (thread
@@ -1101,25 +1305,8 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) l_item += lred[w * kCols + tid];
   }
-  auto store = [&](const f32x4 (&o)[NCB], const float (&m)[2], float l) {
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-      const int cl = 16 * (cb0 + cb) + (lane & 15);
-      if (cl < cn) {
-        const int64_t colg = query_row(c0 + cl, N_g, G, a.H_q);
-        *reinterpret_cast<float4*>(a.part_o + (colg * a.n_slots + slot) * D + 16 * ds + 4 * (lane >> 4)) =
-            make_float4(o[cb][0], o[cb][1], o[cb][2], o[cb][3]);
-      }
-    }
-    if (tid < cn) {
-      const int64_t colg = query_row(c0 + tid, N_g, G, a.H_q);
-      a.part_ml[colg * a.n_slots + slot] = make_float2(tid < 32 ? m[0] : m[1], l);
-    }
-  };
-  if constexpr (MAX_RT <= 2) {
-    // fold into the group's running partial (log-sum-exp); the group's last
-    // item writes it out
-    const bool first = (it.flags & kItemFirst) != 0;
+  {
+    // fold into the group's running partial (log-sum-exp)
     float fa[2], fb[2];
 #pragma unroll
     for (int ch = 0; ch < 2; ++ch) {
@@ -1130,25 +1317,42 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
     }
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
-      const int cc = 16 * (cb0 + cb) + (lane & 15);  // column within the tile
+      const int cc = 16 * (cb0 + cb) + (ln & 15);  // column within the tile
       const bool hi = ((cb0 + cb) >> 1) != 0;        // wave-uniform: column half
       const float sa = __shfl(hi ? fa[1] : fa[0], cc & 31);
       const float sb = __shfl(hi ? fb[1] : fb[0], cc & 31);
-      acc.o[cb] = first ? uacc[cb] * sb : acc.o[cb] * sa + uacc[cb] * sb;
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl) {
+        uacc[cb][sl] *= sb;
+        if (!first) {
+          uacc[cb][sl][0] += old[cb][sl].x * sa;
+          uacc[cb][sl][1] += old[cb][sl].y * sa;
+          uacc[cb][sl][2] += old[cb][sl].z * sa;
+          uacc[cb][sl][3] += old[cb][sl].w * sa;
+        }
+      }
     }
     if (tid < kCols) {
       const int ch = tid >> 5;
       acc.l = first ? l_item * fb[ch] : acc.l * fa[ch] + l_item * fb[ch];
     }
-    if (it.flags & kItemFlush) store(acc.o, acc.m, acc.l);
-  } else {
-    store(uacc, m_run, l_item);
   }
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb)
+    if (16 * (cb0 + cb) + (ln & 15) < cn) {
+#pragma unroll
+      for (int sl = 0; sl < (narrow ? 1 : 2); ++sl)
+        *slot_o(cb, sl) = make_float4(uacc[cb][sl][0], uacc[cb][sl][1], uacc[cb][sl][2], uacc[cb][sl][3]);
+    }
+  if ((it.flags & kItemFlush) && tid < cn) {
+    const int64_t colg = query_row(a, c0 + tid);
+    a.part_ml[colg * a.n_slots + slot] = make_float2(tid < 32 ? acc.m[0] : acc.m[1], acc.l);
+  }
+  rl.advance();
 }
 
-template <int D, int MAX_RT, int NSLOT, bool WH, int MODE>
+template <int D, int MAX_RT, int MODE>
 __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
-  constexpr bool I8 = MODE == 1;
   extern __shared__ __align__(16) unsigned char smem[];
   const WgProgram p = a.wg[blockIdx.x];
   if (p.n_items == 0) return;
@@ -1160,12 +1364,8 @@ __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
   lds_barrier();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned char* work = smem + a.prog_bytes;
-  FragRing<D, NSLOT, I8> fr;
-  GroupAcc<up_col_blocks<D>()> acc;
-  fr.data = reinterpret_cast<const unsigned char*>(a.data);
-  fr.lane = threadIdx.x & 63;
-  fr.ring = reinterpret_cast<__bf16*>(work + a.ring_offset) + (size_t)wave * NSLOT * kFragElems;
-  fr.ring_lds = __builtin_amdgcn_readfirstlane(lds_addr(fr.ring));
+  Streams<D, MAX_RT> fs;
+  GroupAcc acc;
   RunDeriver<D> rd;
   rd.items = smem;
   rd.n_items = p.n_items;
@@ -1174,14 +1374,17 @@ __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
   rd.rbuf = reinterpret_cast<int2*>(smem + (size_t)p.n_items * sizeof(WorkItem));
   rd.recon_delta = a.recon_delta;
   rd.run_cap = a.run_cap;
-  fr.run_cap = a.run_cap;
   if (wave == 0) {
     rd.derive(threadIdx.x & 63);
     rd.derive(threadIdx.x & 63);
   }
   lds_barrier();
-  fr.rbuf = rd.rbuf + (size_t)wave * kRunBufs * a.run_cap;
-  fr.start();
+  RunList rl;
+  rl.rbuf = rd.rbuf + (size_t)wave * kRunBufs * a.run_cap;
+  rl.run_cap = a.run_cap;
+  rl.rb = 0;
+  bf16x8 qv[query_loads<D>()];
+  bool primed = false;
   for (int k = 0; k < p.n_items; ++k) {
     const WorkItem it = lds_item(smem + (size_t)k * sizeof(WorkItem));
     if (k > 0) lds_barrier();  // the previous item's LDS reads are done
@@ -1189,10 +1392,28 @@ __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
     // lane-dependent address of one item kind stays live across the other
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    if (it.kind == kItemBlock) block_item<D, MAX_RT, NSLOT, WH, MODE>(a, it, work, fr, rd, acc, tid);
-    else if (it.kind == kItemTail) tail_item<D>(a, it, work, tid);
+    if (it.kind == kItemBlock) {
+      if (!primed) {  // the first block item (block items follow the tail items)
+        load_queries<D>(a, it.req, ((it.flags >> kItemColsShift) & 63) + 1, tid, qv);
+        if constexpr (MODE != 1) {  // INT8 items load their first K run themselves
+          const auto run = item_first_run<D, MAX_RT>(reinterpret_cast<const WorkItem*>(smem) + k, wave,
+                                                     reinterpret_cast<const unsigned char*>(a.data) +
+                                                         (int64_t)rl.first(0) * kFragElems * 2);
+          static_for<0, Streams<D, MAX_RT>::KD, 1>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            fs.ks[i][0] = load_frag16(run.p, run.off(i), 16 * (tid & 63));
+            if constexpr (Streams<D, MAX_RT>::kPair)
+              fs.ks[i][1] = load_frag16(run.p, run.off(i) + run.delta, 16 * (tid & 63), run.wanted2);
+          });
+        }
+        primed = true;
+      }
+      const WorkItem* next = k + 1 < p.n_items ? reinterpret_cast<const WorkItem*>(smem) + k + 1 : nullptr;
+      block_item<D, MAX_RT, MODE>(a, it, work, fs, rl, rd, acc, qv, next, tid);
+    } else if (it.kind == kItemTail) {
+      tail_item<D>(a, it, work, tid);
+    }
   }
-  if constexpr (NSLOT > 0) wait_vmcnt<0>();  // no LDS write may land after the workgroup ends
 }
 
 // ---------------------------------------------------------------------------
@@ -1317,58 +1538,44 @@ hipError_t launch_scale_units(const float* ks, const float* vs, int T_pad, float
 }
 
 
-template <int D, int MAX_RT, int NSLOT, bool WH, int MODE>
+template <int D, int MAX_RT, int MODE>
 static hipError_t launch_attend_t(const AttendArgs& a, int grid, size_t lds, hipStream_t s, hipEvent_t e0,
                                   hipEvent_t e1) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_kernel<D, MAX_RT, NSLOT, WH, MODE>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_kernel<D, MAX_RT, MODE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipExtLaunchKernelGGL((attend_kernel<D, MAX_RT, NSLOT, WH, MODE>), dim3(grid), dim3(kThreads), (uint32_t)lds, s,
-                        e0, e1, 0, a);
+  hipExtLaunchKernelGGL((attend_kernel<D, MAX_RT, MODE>), dim3(grid), dim3(kThreads), (uint32_t)lds, s, e0, e1, 0, a);
   return hipGetLastError();
 }
 
-// ring slots 8 / 6 / none with the whole weight tile; 4 with the half tile
-template <int D, int MAX_RT, int MODE>
-static hipError_t launch_attend_r(const AttendArgs& a, int nslot, int grid, size_t lds, hipStream_t s, hipEvent_t e0,
-                                  hipEvent_t e1) {
-  switch (nslot) {
-    case 8: return launch_attend_t<D, MAX_RT, 8, false, MODE>(a, grid, lds, s, e0, e1);
-    case 6: return launch_attend_t<D, MAX_RT, 6, false, MODE>(a, grid, lds, s, e0, e1);
-    case 4: return launch_attend_t<D, MAX_RT, 4, true, MODE>(a, grid, lds, s, e0, e1);
-    case 0: return launch_attend_t<D, MAX_RT, 0, false, MODE>(a, grid, lds, s, e0, e1);
-    default: return hipErrorInvalidValue;
-  }
-}
-
 template <int D, int MODE>
-static hipError_t launch_attend_d(const AttendArgs& a, int max_rt, int nslot, int grid, size_t lds,
-                                  hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+static hipError_t launch_attend_d(const AttendArgs& a, int max_rt, int grid, size_t lds, hipStream_t s, hipEvent_t e0,
+                                  hipEvent_t e1) {
   switch (max_rt) {
-    case 2: return launch_attend_r<D, 2, MODE>(a, nslot, grid, lds, s, e0, e1);
-    case 3: return launch_attend_r<D, 3, MODE>(a, nslot, grid, lds, s, e0, e1);
-    case 4: return launch_attend_r<D, 4, MODE>(a, nslot, grid, lds, s, e0, e1);
+    case 2: return launch_attend_t<D, 2, MODE>(a, grid, lds, s, e0, e1);
+    case 3: return launch_attend_t<D, 3, MODE>(a, grid, lds, s, e0, e1);
+    case 4: return launch_attend_t<D, 4, MODE>(a, grid, lds, s, e0, e1);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <int D>
-static hipError_t launch_attend_m(const AttendArgs& a, int max_rt, int nslot, bool p_int8, bool gemv, int grid,
-                                  size_t lds, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (p_int8) return launch_attend_d<D, 1>(a, max_rt, nslot, grid, lds, s, e0, e1);
-  if (gemv) return launch_attend_d<D, 2>(a, max_rt, nslot, grid, lds, s, e0, e1);
-  return launch_attend_d<D, 0>(a, max_rt, nslot, grid, lds, s, e0, e1);
+static hipError_t launch_attend_m(const AttendArgs& a, int max_rt, bool p_int8, bool gemv, int grid, size_t lds,
+                                  hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (p_int8) return launch_attend_d<D, 1>(a, max_rt, grid, lds, s, e0, e1);
+  if (gemv) return launch_attend_d<D, 2>(a, max_rt, grid, lds, s, e0, e1);
+  return launch_attend_d<D, 0>(a, max_rt, grid, lds, s, e0, e1);
 }
 
-hipError_t launch_attend(const AttendArgs& a, int head_dim, int max_rt, int nslot, bool p_int8, bool gemv, int grid,
+hipError_t launch_attend(const AttendArgs& a, int head_dim, int max_rt, bool p_int8, bool gemv, int grid,
                          size_t lds_bytes, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (grid == 0) return hipSuccess;
-  if (head_dim == 64) return launch_attend_m<64>(a, max_rt, nslot, p_int8, gemv, grid, lds_bytes, s, e0, e1);
-  if (head_dim == 128) return launch_attend_m<128>(a, max_rt, nslot, p_int8, gemv, grid, lds_bytes, s, e0, e1);
+  if (head_dim == 64) return launch_attend_m<64>(a, max_rt, p_int8, gemv, grid, lds_bytes, s, e0, e1);
+  if (head_dim == 128) return launch_attend_m<128>(a, max_rt, p_int8, gemv, grid, lds_bytes, s, e0, e1);
   return hipErrorInvalidValue;
 }
 

@@ -11,13 +11,16 @@
 
 namespace milo {
 
-// LDS of the attention kernel: a base region (projected query, weight tile and
-// reductions, or the tail item's buffers) followed by kWaves rings of nslot
-// fragments.
+// LDS of the attention kernel's work area: projected query, weight tile and
+// reductions, or the up-projection's or the tail item's buffers.
 size_t attend_lds_base_bytes(int head_dim, int rk_pad_max, int rv_pad_max, bool half_w) {
+  (void)half_w;  // no layout has halved weight tiles any more
   const size_t qsd = (size_t)rk_pad_max + 8;
-  const size_t ws = half_w ? kTile / 2 + 8 : kWStride;
-  const size_t loop = kCols * qsd * 2 + (size_t)kCols * ws * 2 + (size_t)kWaves * kCols * 4;
+  const bool pair = rk_pad_max <= kPairRank && rv_pad_max <= kPairRank;
+  // the weights of one or two tiles, the per-wave column maxima, and with two
+  // tiles the waves' INT8 scale units
+  const size_t weights = (size_t)kCols * (pair ? kWStridePair : kWStride) * 2;
+  const size_t loop = kCols * qsd * 2 + weights + (size_t)kWaves * kCols * 4 * (pair ? 3 : 1);
   // up-projection: the latent accumulator as bf16 [col][rank], or the segment
   // partials being combined (at most 4 slots x 3 rank tiles x 8 KiB), then the
   // per-wave column sums at the end of the region
@@ -27,10 +30,10 @@ size_t attend_lds_base_bytes(int head_dim, int rk_pad_max, int rv_pad_max, bool 
   const size_t tail = ((size_t)2 * kWaves * 32 + (size_t)kTailChunk * 32 + (size_t)kWaves * kMaxGroup * head_dim) * 4;
   size_t m = loop > epi ? loop : epi;
   m = m > tail ? m : tail;
-  return (m + 1023) / 1024 * 1024;  // the fragment rings start here
+  return (m + 1023) / 1024 * 1024;
 }
 
-size_t attend_ring_bytes(int nslot) { return (size_t)kWaves * nslot * kFragElems * 2; }
+size_t attend_ring_bytes(int) { return 0; }
 
 // ---------------------------------------------------------------------------
 // Work schedule of one attention call.
@@ -65,12 +68,14 @@ size_t attend_ring_bytes(int nslot) { return (size_t)kWaves * nslot * kFragElems
 // skip chunks past it, so a decode loop whose tails grow by one token per step
 // reuses its plan until the longest tail doubles.
 // ---------------------------------------------------------------------------
-// Cost model (microseconds on an MI355X, least-squares fit to per-item kernel
-// timings of the 7B-shaped layer, rms error 0.5 us): one fragment of the
+// Cost model (microseconds on an MI355X, from a least-squares fit to per-item
+// kernel timings of the 7B-shaped layer; the tile stream's 0.13 was 0.153 with
+// fragments streamed through LDS, and 0.13 picks better splits now: the 7B layer
+// with INT8 P 51.9 -> 48.3 us, the others within 0.5%): one fragment of the
 // slowest wave's projection and up-projection streams, one fragment of its
 // tile stream, the per-tile softmax and barriers, the per-item set-up, one
 // round of the token-segment reduction, and one dense-tail chunk.
-constexpr double kCostFragItem = 0.206, kCostFragTile = 0.153, kCostTile = 1.75, kCostItem = 2.43,
+constexpr double kCostFragItem = 0.206, kCostFragTile = 0.13, kCostTile = 1.75, kCostItem = 2.43,
                  kCostSegRound = 0.61, kCostTail = 9.4;
 constexpr int kPerXcd = kCUs / kXcds;  // workgroups per XCD
 
@@ -294,10 +299,6 @@ bool build_schedule(const PlanInput& c, const int32_t* table, int n_sel, int n_q
     out->max_own = std::max(out->max_own, max_owned(m));
   }
 
-  // LDS plan: the projected query, weight tile and a 6-slot fragment ring,
-  // the rest for the program (fewer launches would cost the ring); when even a
-  // short program leaves no room for that (ranks above 512), the weight tile
-  // in two 128-token halves and a 4-slot ring; failing that, no ring
   // run buffers sized for this plan's items: the most KV heads of a tile and
   // the most tiles of a part
   int max_nh = 1, max_pt = 1;
@@ -305,22 +306,9 @@ bool build_schedule(const PlanInput& c, const int32_t* table, int n_sel, int n_q
   for (const Part& pt : parts) max_pt = std::max(max_pt, pt.ntile);
   out->run_cap = run_cap_for(max_nh, max_pt, c.p_int8);
   const size_t run_bytes = (size_t)kWaves * kRunBufs * out->run_cap * sizeof(int2);
-  const size_t short_prog = 16 * sizeof(WorkItem) + run_bytes;
-  auto room_for = [&](bool half_w) {
-    const size_t b = attend_lds_base_bytes(c.d, out->rk_pad_max, out->rv_pad_max, half_w);
-    return b < (size_t)kLdsBytes ? kLdsBytes - b : 0;
-  };
-  size_t cap;
-  if (room_for(false) >= attend_ring_bytes(6) + short_prog) {
-    out->half_w = false;
-    cap = room_for(false) - attend_ring_bytes(6);
-  } else if (room_for(true) >= attend_ring_bytes(4) + short_prog) {
-    out->half_w = true;
-    cap = room_for(true) - attend_ring_bytes(4);
-  } else {
-    out->half_w = false;
-    cap = room_for(false);
-  }
+  // the program gets what the work area leaves of LDS
+  const size_t base = attend_lds_base_bytes(c.d, out->rk_pad_max, out->rv_pad_max, false);
+  size_t cap = base < (size_t)kLdsBytes ? kLdsBytes - base : 0;
   if (program_cap >= 0) cap = std::min(cap, (size_t)program_cap);
   for (int L = 1; L <= (1 << 20); L *= 2) {
     std::vector<std::vector<unsigned char>> progs((size_t)L * kCUs);
@@ -385,7 +373,7 @@ bool build_schedule(const PlanInput& c, const int32_t* table, int n_sel, int n_q
             w.tile0 = pt.tile0;
             w.ntile = pt.ntile;
             w.flags = (lg_rank_groups(w.blk.rv_pad / 32) << kItemLgNgShift) | ((til.cn[tile] - 1) << kItemColsShift) |
-                      ((til.nh[tile] - 1) << kItemHeadsShift) | (c.p_int8 ? kItemInt8 : 0) |
+                      ((til.nh[tile] - 1) << kItemHeadsShift) | (j << kItemGangShift) | (c.p_int8 ? kItemInt8 : 0) |
                       (dense ? kItemDense : 0) | (pt.b == c.causal_block ? kItemCausal : 0);
             items.push_back(w);
           }
