@@ -615,21 +615,23 @@ class CacheWorkspace : public Workspace {
 };
 
 // Reconstruct-then-attend pays for a block when rebuilding its keys and values
-// and attending them densely is clearly faster than the latent route.  Per-block
-// times (microseconds) fitted to MI355X kernel timings of the 7B- (28-layer) and
+// and attending them densely is faster than the latent route.  Per-block times
+// (microseconds) fitted to MI355X kernel timings of the 7B- (28-layer) and
 // 14B-shaped steps, for a block of T tokens, ranks rk / rv, N query columns,
 // D = H_kv d:
-//   latent        4.24e-9 N (rk + rv)(T + d)        (latent block items)
+//   latent        2.65e-9 N (rk + rv)(T + d)        (latent block items)
 //   reconstruct   4.17e-9 T D (rk + rv)             (reconstruction GEMMs)
 //               + 1.99e-6 T D                       (writing, then reading, the 16-bit K and V)
 //               + 7.06e-9 N T d                     (dense block items)
-// and reconstruction is chosen below 0.85 of the latent time (mixed plans
-// measured slower than the sum of their parts near the tie).
+// and reconstruction is chosen below 0.95 of the latent time: in the 14B-shaped
+// 64-query step the ranks of 768 alone.  (Before fragments streamed through
+// registers the latent constant was 4.24e-9 and every rank from 448 on was
+// rebuilt; that choice now takes 2056 us where the latent route takes 1783.)
 bool recon_pays(int T, int rk, int rv, int64_t N, int D, int d) {
   const double r = (double)rk + rv;
-  const double lat = 4.24e-9 * (double)N * r * (T + d);
+  const double lat = 2.65e-9 * (double)N * r * (T + d);
   const double rec = 4.17e-9 * (double)T * D * r + 1.99e-6 * (double)T * D + 7.06e-9 * (double)N * T * d;
-  return rec < 0.85 * lat;
+  return rec < 0.95 * lat;
 }
 
 }  // namespace
