@@ -810,16 +810,16 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
       std::memcpy(sch.bytes.data() + rb_off, rp.blocks.data(), rp.blocks.size() * sizeof(ReconBlock));
       std::memcpy(sch.bytes.data() + rt_off, rp.tasks.data(), rp.tasks.size() * sizeof(int2));
     }
-    // Kernel variant by the rank tiles a wave owns: up to two, the one that takes
-    // tiles in pairs (half the LDS reads per score); else the ones that take
-    // single tiles and fetch ahead for the gang.  Few columns that share P leave a
-    // step bound by how fast P comes from HBM, and there fetching ahead is worth
-    // more: 224 columns (7B layer, 8 requests) 56.2 us single against 59.8 in
-    // pairs, 640 (1M tokens, 16 requests) 1445 against 1501; at 896 columns 208
-    // against 198, with INT8 P (half the bytes) 57.2 against 53.4, on rebuilt
-    // blocks (640 columns) 287 against 281; a gang of one shares nothing.
-    int max_rt = sch.max_own <= 2 ? 2 : sch.max_own == 3 ? 3 : 4;
-    if (max_rt == 2 && sch.gang > 1 && n_cols <= kFetchAheadCols && !c->p_int8 && n_recon == 0 && !shared_tail) max_rt = 3;
+    // Kernel variant by the rank tiles a wave owns.  With up to two, the gang's
+    // workgroups fetch the coming tile's P into L2 between them only where its P is
+    // long (kFetchRanks) and several share it (kFetchGang): from there on it costs
+    // 0-3% on factors that sit in the last-level cache and gains 2-20% on ones that
+    // do not (7B layer, 8 requests, mean rank 582, gang of 4: 44.9 / 83.5 -> 44.9 /
+    // 73.2 us, 1M tokens, 650, gang of 10: 1463 / 1492 -> 1381 / 1374); at mean ranks
+    // of 30-250 it loses 2-6% and 0-5%, in gangs of two it gains nothing.
+    constexpr int kFetchRanks = 512, kFetchGang = 4;
+    const int max_rt = sch.max_own <= 2 ? 2 : sch.max_own == 3 ? 3 : 4;
+    const bool fetch = max_rt > 2 || (sch.gang >= kFetchGang && sch.mean_ranks >= kFetchRanks);
     const size_t base = attend_lds_base_bytes(c->d, sch.rk_pad_max, sch.rv_pad_max, sch.half_w);
     const size_t prog = (size_t)sch.prog_bytes;
     // the workspace for the new plan's partials first (a workspace that cannot
@@ -841,6 +841,7 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
     ps.count_off = sch.count_off;
     ps.tiles = til.geom;
     ps.max_rt = max_rt;
+    ps.fetch = fetch;
     ps.rk_pad_max = sch.rk_pad_max;
     ps.prog_bytes = sch.prog_bytes;
     ps.work_bytes = (int)base;
@@ -989,7 +990,7 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
   }
   for (int l = 0; l < ps.n_launch; ++l) {
     aa.wg = reinterpret_cast<const WgProgram*>(ps.plan_d) + (size_t)l * kCUs;
-    e = launch_attend(aa, c->d, ps.max_rt, c->p_int8, ps.gemv, kCUs, ps.lds, s, l == 0 ? ev[0] : nullptr,
+    e = launch_attend(aa, c->d, ps.max_rt, ps.fetch, c->p_int8, ps.gemv, kCUs, ps.lds, s, l == 0 ? ev[0] : nullptr,
                       l == ps.n_launch - 1 ? ev[1] : nullptr);
     if (e != hipSuccess) return launch_fail(e, "attend kernel launch");
   }

@@ -89,8 +89,7 @@ struct BlockMeta {
 // scale per token row, P[t][k] = s_t c[t][k] (s_t = max_k |P[t][k]| / 127,
 // c = round-to-nearest-even(P / s_t), both in fp32).  Codes keep the fragment
 // order above at one byte per element (a fragment is 512 bytes: lane l's 8
-// codes at bytes 8l..8l+7), so one 1 KiB unit of the fragment stream holds two
-// consecutive fragments of a run.  Each block's scales follow its P^V codes
+// codes at bytes 8l..8l+7; a register slot holds one).  Each block's scales follow its P^V codes
 // as 256-byte units, one per (256-token tile t, wave w): the K scales of the
 // wave's 32 score tokens 256t + 32w + m (m = 0..31), then their V scales.
 constexpr int kScaleUnitBytes = 256;
@@ -413,7 +412,8 @@ struct WgProgram {
   int64_t off;                // byte offset in the program buffer (16-byte aligned)
   int32_t words;              // program size in 4-byte words
   int32_t n_items;            // work items (they start the program)
-  int32_t pad[2];
+  int32_t first_block;        // the first block item (block items follow the tail items; n_items: none)
+  int32_t pad;
 };
 static_assert(sizeof(WgProgram) == 24, "program entry layout");
 // Bytes the attention kernel's fragment loads may read past the end of a run:
@@ -426,12 +426,7 @@ constexpr int kCols = 64;                      // query columns per workgroup
 constexpr int kGemvCols = 16;                  // most columns of a tile whose projection may run as a GEMV
 constexpr int kTokWave = kTile / kWaves;       // tokens per wave per tile (one MFMA row block)
 static_assert(kTokWave == 32, "the score pass gives every wave one 32-token sub-tile");
-constexpr int kWStride = kTile + 8;            // bf16 row stride of one tile's weights in LDS
-constexpr int kWStridePair = 2 * kTile + 8;    // of two tiles' weights
-// Where every block of a plan has ranks up to kPairRank the kernel takes two
-// 256-token tiles per step (no wave then owns more than kMaxOwn rank tiles).
-constexpr int kPairRank = 32 * kWaves * kMaxOwn;
-constexpr int kFetchAheadCols = 768;           // most columns of a step that takes single tiles at ranks <= kPairRank
+constexpr int kWStride = kTile + 8;            // bf16 row stride of a tile's weights in LDS
 constexpr int kMaxGroup = 16;                  // max query heads per KV head
 constexpr int kMaxRank = 896;                  // largest rank of the latent route (LDS bound)
 constexpr int kMaxStoredRank = 1024;           // largest rank a cache stores (higher-rank blocks are reconstructed)
@@ -553,9 +548,11 @@ hipError_t launch_row_scales(const uint16_t* src, int rows, int cols, int rows_p
 hipError_t launch_scale_units(const float* ks, const float* vs, int T_pad, float* dst, hipStream_t s);
 // e0 / e1 (may be null): events recorded when the kernel starts and ends
 // (hipExtLaunchKernelGGL), so they time the kernel itself.
+// fetch: the kernel variant whose gangs fetch the coming tile's P into L2 (variants
+// of three and four rank tiles per wave always do)
 // gemv: the kernel variant whose latent projection is a wavefront GEMV (tiles
 // of at most kGemvCols columns; bf16 P factors only)
-hipError_t launch_attend(const AttendArgs& a, int head_dim, int max_rt, bool p_int8, bool gemv, int grid,
+hipError_t launch_attend(const AttendArgs& a, int head_dim, int max_rt, bool fetch, bool p_int8, bool gemv, int grid,
                          size_t lds_bytes, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_merge(const MergeArgs& a, int head_dim, int n_cols, hipStream_t s, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr);

@@ -328,7 +328,7 @@ __device__ __forceinline__ void tail_item(const AttendArgs& a, const WorkItem& i
   if (G <= 8) tail_values<D, 8>(wt + kTokW * wave * 32, vraw, op + wave * kMaxGroup * D + DL * lane);
   else tail_values<D, kMaxGroup>(wt + kTokW * wave * 32, vraw, op + wave * kMaxGroup * D + DL * lane);
   lds_barrier();
-  for (int x = tid; x < G * D; x += kThreads) {
+  for (unsigned x = tid; x < (unsigned)(G * D); x += kThreads) {
     const int h = x / D, dd = x % D;
     float o = 0.f;
 #pragma unroll
@@ -381,23 +381,19 @@ __device__ __forceinline__ WorkItem lds_item(const unsigned char* p) {
 // kernel did before, cost two LDS passes and ~16 scalar instructions per
 // fragment.)
 //
-// kPair (at most two latent rank tiles per wave, ranks up to 512): tiles are
-// taken two at a time, every wave scoring 64 tokens, so that one LDS read of a
-// Qt operand feeds two MFMAs.  With 32 tokens per wave the eight waves ask LDS
-// for 128 bytes per clock, all it has, as soon as the MFMAs run back to back.
-// Above that rank neither the registers nor LDS hold two tiles.  Measured, with
-// register streams against the LDS rings: 7B layer of 32 requests 211 -> 198 us,
-// prefill of 256 tokens 886 -> 808; ranks to 768 (single tiles) 2800 -> 1783.
-// What bounds a tile now is P on its way from L2: a bare loop of these loads and
-// MFMAs reaches 1260-1400 TFLOP/s against 64 columns, 1900-2160 without loads.
-template <int D, int MAX_RT>
+// Measured, register streams against the LDS rings: 14B layer of 64 requests (ranks
+// to 768) 2796 -> 1697 us, 7B layer of 32 requests 199 -> 172, prefill of 256 tokens
+// 864 -> 743, 1M tokens 1574 -> 1371; one-tile blocks of ranks 17 .. 44 under a
+// prefill of 228 tokens, where an item's set-up is all its time, 215 -> 214.
+// (Two tiles per step, which halves the LDS reads per score, was measured too: the
+// registers it takes send the group's output through memory, and it gained 2-5% on
+// long items and lost up to 14% on short ones.)
+template <int D>
 struct Streams {
-  static constexpr bool kPair = MAX_RT == 2;
-  static constexpr int KD = 4;               // steps in a round of ks
-  static constexpr int NS = kPair ? 2 : 1;   // fragments per step: token sub-tiles, or R^K steps i and i + KD
-  static constexpr int VD = 4;               // P^V fragments loaded ahead across tiles
+  static constexpr int KD = 4;  // steps in a round of ks
+  static constexpr int VD = 4;  // P^V fragments loaded ahead across tiles
   static_assert(KD * 1024 <= kOverread, "reads past a run stay inside its buffer");
-  bf16x8 ks[KD][NS], vs[VD];
+  bf16x8 ks[KD], vs[VD];
 };
 
 // f(integral constant i) for i = FROM, FROM + STEP, .. below TO
@@ -426,40 +422,41 @@ __device__ __forceinline__ bf16x8 load_frag16(const unsigned char* p, int off, i
 __device__ __forceinline__ uint2 load_frag8(const unsigned char* p, int off, int lane8, int wanted) {
   return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(frag_buffer(p, wanted), lane8, off, 0));
 }
+// Behind a slot's reload in the rounds of the tile loop: neither memory accesses
+// nor MFMAs move across it (VALU, SALU and LDS may).  The scheduler otherwise
+// gathers a round's reloads behind its MFMAs, which leaves 2 to 5 loads in flight
+// where 7 could be.  Not where an item starts: there it costs a short item 2%.
+__device__ __forceinline__ void pin_load() { __builtin_amdgcn_sched_barrier(0x0086); }
 // Where the slots of a set of N find their first steps of a run of n steps at p
-// (fragments of B bytes): slot s holds step (s + n) mod N, and in its second
-// fragment (kPair) what lies delta bytes on.  n = 0: no run.
+// (fragments of B bytes): slot s holds step (s + n) mod N.  n = 0: no run.
 template <int N, int B>
 struct RunStart {
   const unsigned char* p;
-  int odd, wanted, delta, wanted2;
-  __device__ __forceinline__ RunStart(const unsigned char* p_, int n, int delta_, int wanted2_)
-      : p(p_), odd(n & (N - 1)), wanted(mask_lt(0, n)), delta(delta_), wanted2(wanted2_) {}
+  int odd, wanted;
+  __device__ __forceinline__ RunStart(const unsigned char* p_, int n) : p(p_), odd(n & (N - 1)), wanted(mask_lt(0, n)) {}
   __device__ __forceinline__ int off(int s) const { return (s + odd - (s + odd >= N ? N : 0)) * B; }
 };
-// Consume a run of n steps (an even number) at p, whose second fragments lie
-// delta bytes on (wanted2: -1, or 0 for none), through slots 0 .. N-1: use(f, s)
-// takes slot s for step f + s, load(s, q, off, wanted, delta, wanted2) reloads it
-// from q + off; next: the set's next run.  The odd steps before the whole rounds
-// are one straight piece of code per count, so that their operand reads overlap;
-// step by step behind branches they cost as much as two rounds.
+// Consume a run of n steps (an even number) at p through slots 0 .. N-1: use(f, s)
+// takes slot s for step f + s, load(s, q, off, wanted) reloads it from q + off;
+// next: the set's next run.  The odd steps before the whole rounds are one
+// straight piece of code per count, so that their operand reads overlap; step by
+// step behind branches they cost as much as two rounds.
 template <int N, int B, typename Use, typename Load>
-__device__ __forceinline__ void consume_run(const unsigned char* p, int n, int delta, int wanted2,
-                                            const RunStart<N, B>& next, Use&& use, Load&& load) {
+__device__ __forceinline__ void consume_run(const unsigned char* p, int n, const RunStart<N, B>& next, Use&& use,
+                                            Load&& load) {
   const int odd = n & (N - 1);
   const bool more = n >= N;
   static_for<2, N, 2>([&](auto odd_c) {
     constexpr int ODD = decltype(odd_c)::value;
     if (odd != ODD) return;
     if (!more) {  // a run shorter than a round: the slots it leaves out move on too
-      static_for<0, N - ODD, 1>([&](auto s) { load(s, next.p, next.off(s), next.wanted, next.delta, next.wanted2); });
+      static_for<0, N - ODD, 1>([&](auto s) { load(s, next.p, next.off(s), next.wanted); });
     }
     const unsigned char* q = more ? p : next.p;
-    const int wanted = mask_lt(N - 1, n) | next.wanted, d = more ? delta : next.delta;
-    const int w2 = more ? wanted2 : next.wanted2;
+    const int wanted = mask_lt(N - 1, n) | next.wanted;
     static_for<N - ODD, N, 1>([&](auto s) {
       use(ODD - N, s);
-      load(s, q, more ? (ODD + s) * B : next.off(s), wanted, d, w2);
+      load(s, q, more ? (ODD + s) * B : next.off(s), wanted);
     });
   });
 #pragma clang loop unroll(disable)
@@ -468,30 +465,28 @@ __device__ __forceinline__ void consume_run(const unsigned char* p, int n, int d
     const int wanted = mask_lt(f + N, n) | next.wanted;
     const unsigned char* q = last ? next.p : p;
     const int lo = last ? next.odd * B : (f + N) * B, hi = last ? lo - N * B : lo, wrap = N - next.odd;
-    const int d = last ? next.delta : delta, w2 = last ? next.wanted2 : wanted2;
     static_for<0, N, 1>([&](auto s) {
       use(f, s);
-      load(s, q, (s < wrap ? lo : hi) + s * B, wanted, d, w2);
+      load(s, q, (s < wrap ? lo : hi) + s * B, wanted);
+      pin_load();
     });
   }
 }
 
 // The first run of a block item (bf16 P factors) for wave `wave`, at p: R^K if
-// the wave owns projection rank tiles, else the first tiles' P^K
-template <int D, int MAX_RT>
-__device__ __forceinline__ RunStart<Streams<D, MAX_RT>::KD, kFragElems * 2> item_first_run(const WorkItem* it, int wave,
-                                                                                             const unsigned char* p) {
-  constexpr int B = kFragElems * 2, KD = Streams<D, MAX_RT>::KD;
-  const int rk_pad = __builtin_amdgcn_readfirstlane(it->blk.rk_pad), ntile = __builtin_amdgcn_readfirstlane(it->ntile);
+// the wave owns projection rank tiles, else the first tile's P^K
+template <int D>
+__device__ __forceinline__ RunStart<Streams<D>::KD, kFragElems * 2> item_first_run(const WorkItem* it, int wave,
+                                                                                   const unsigned char* p) {
+  const int rk_pad = __builtin_amdgcn_readfirstlane(it->blk.rk_pad);
   const bool dense = (__builtin_amdgcn_readfirstlane(it->flags) & kItemDense) != 0;
   const bool rk = !dense && owned_tiles(rk_pad >> 5, wave, kWaves) > 0;
-  return RunStart<KD, B>(p, rk ? KD : rk_pad >> 4, rk ? KD * B : (rk_pad >> 4) * B,
-                         rk ? -(int)(D / 16 > KD) : mask_lt(1, ntile));
+  return RunStart<Streams<D>::KD, kFragElems * 2>(p, rk ? Streams<D>::KD : rk_pad >> 4);
 }
 
 // The waves' run lists: for each of its block items a wave finds the first
-// fragment of the runs it consumes (block_runs) in an LDS buffer that wave 0
-// fills for all eight waves (RunDeriver) two block items ahead, four buffers
+// fragment of the runs it consumes (block_runs) in an LDS buffer that the last wave
+// fills for all eight (RunDeriver) two block items ahead, four buffers
 // used in turn: the buffer being refilled is two items behind, and the next
 // item's list is complete while the current item runs.  After the last block
 // item a run of the buffer's first fragments follows (loaded, never used).
@@ -505,8 +500,9 @@ struct RunList {
   __device__ __forceinline__ void advance() { rb = (rb + 1) % kRunBufs; }
 };
 
-// Derivation of the run lists, done by wave 0 for all eight waves (lane w
-// derives wave w's runs, in vector registers): the runs of the workgroup's
+// Derivation of the run lists, done by the last wave for all eight (lane w
+// derives wave w's runs, in vector registers) while the others project: it owns
+// the fewest projection rank tiles, none up to rank 224: the runs of the workgroup's
 // next block item, or the closing run after the last one, into every wave's
 // buffer gb.  Runs are read by their wave only after a later workgroup
 // barrier.
@@ -546,14 +542,22 @@ struct RunDeriver {
 };
 
 // A workgroup's running partial for its current group of block items (one KV
-// head and column tile): the per-column maximum in the score layout (32 ch +
-// lane % 32; every wave holds it) and the per-column sum in wave 0 (thread t:
-// column t).  The output is folded in place in the group's slot, each thread
-// reading back what it wrote (registers for it would spill the tile loop).
+// head and column tile): the output in the up-projection's layout (NCB 16-column
+// blocks of two 16-dim slices), the per-column maximum in the score layout (32 ch +
+// lane % 32; every wave holds it), the per-column sum in wave 0 (thread t: column
+// t).  Only plans of at most two rank tiles per wave fold items into groups.
+// (Folding in place in the group's slot instead cost a short item 1.1 of its 10 us:
+// the stores sit in the same in-order count as the streams' loads.)
+template <int NCB>
 struct GroupAcc {
+  f32x4 o[NCB][2];
   float m[2];
   float l;
 };
+template <int D>
+constexpr int up_col_blocks() {
+  return D / 64;  // 16-column blocks per wave in the up-projection (two slices)
+}
 // 16-byte chunks of an item's query rows a thread loads, and the load: chunk x
 // of the 64 rows of a column tile (first column c0, cn columns)
 template <int D>
@@ -592,16 +596,15 @@ __device__ __forceinline__ void load_queries(const AttendArgs& a, int c0, int cn
 // MODE: 0 bf16 P factors, 1 INT8 P factors, 2 bf16 P factors with the
 // projection as a wavefront GEMV (kernel variants, so no branch of one costs
 // the others registers)
-template <int D, int MAX_RT, int MODE>
+// FETCH: the gang's workgroups fetch the coming tile's P into L2 between them
+template <int D, int MAX_RT, bool FETCH, int MODE>
 __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& it, unsigned char* smem,
-                                           Streams<D, MAX_RT>& fs, RunList& rl, RunDeriver<D>& rd,
-                                           GroupAcc& acc, bf16x8 (&qv)[query_loads<D>()], const WorkItem* next_item,
+                                           Streams<D>& fs, RunList& rl, RunDeriver<D>& rd,
+                                           GroupAcc<up_col_blocks<D>()>& acc, bf16x8 (&qv)[query_loads<D>()], const WorkItem* next_item,
                                            const int tid) {
   constexpr bool I8 = MODE == 1, GV = MODE == 2;
   constexpr int NK = D / 16;
-  constexpr int KD = Streams<D, MAX_RT>::KD;
-  constexpr int NS = Streams<D, MAX_RT>::NS, VD = Streams<D, MAX_RT>::VD;
-  constexpr bool kPair = Streams<D, MAX_RT>::kPair;
+  constexpr int KD = Streams<D>::KD, VD = Streams<D>::VD;
   static_assert(NK == KD || NK == 2 * KD, "an R^K rank tile is one or two rounds");
   const BlockMeta& bm = it.blk;
   const int slot = it.slot, g0 = it.g, c0 = it.req;
@@ -620,12 +623,14 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
   const int nrt_k = bm.rk_pad >> 5, nks = bm.rk_pad >> 4;
   const int nrt_v = bm.rv_pad >> 5;
   const int own_k = owned_tiles(nrt_k, wave, kWaves);
-  const int nseg = v_segments(nrt_v), ng = kWaves / nseg;
-  const int rg = wave % ng, sg = wave / ng;
-  const int own_v = owned_tiles(nrt_v, rg, ng);
-  const int nst = 16 / nseg;                // 16-token steps of the wave's segment per tile
+  // the split of the value pass, nseg = 8 / ng segments x ng = 2^lg_ng rank groups
+  // (v_segments); shifts, since divisions by ng cost a short item half a microsecond
+  const int lg_ng = (it.flags >> kItemLgNgShift) & 3, ng = 1 << lg_ng, nseg = kWaves >> lg_ng;
+  const int rg = wave & (ng - 1), sg = wave >> lg_ng;
+  const int own_v = (nrt_v >> lg_ng) + (rg < (nrt_v & (ng - 1)) ? 1 : 0);
+  const int nst = 2 << lg_ng;               // 16-token steps of the wave's segment per tile
   const int T = bm.T;
-  constexpr int kTouches = kPair ? 0 : 2;  // lines a lane fetches ahead for the gang per tile
+  constexpr int kTouches = FETCH ? 2 : 0;  // lines a lane fetches ahead for the gang per tile
   const int gang_at = (it.flags >> kItemGangShift) & 31;
   const int ntiles = it.ntile, tile0 = it.tile0;  // tiles this item covers
   // causal limits of this lane's two columns (32 ch + lane % 32; request (c mod N_g) / G)
@@ -642,10 +647,9 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
     for (int off = 32; off > 0; off >>= 1) lim_min = min(lim_min, __shfl_xor(lim_min, off));
   }
   __bf16* qt = reinterpret_cast<__bf16*>(smem);             // [kCols][qsd]
-  constexpr int kWS = kPair ? kWStridePair : kWStride;
-  __bf16* wl = qt + kCols * qsd;                            // [kCols][kWS] the weights of one or two tiles
+  constexpr int kWS = kWStride;
+  __bf16* wl = qt + kCols * qsd;                            // [kCols][kWS] the tile's weights
   float* red = reinterpret_cast<float*>(wl + kCols * kWS);  // [kWaves][kCols]
-  float* units = red + kWaves * kCols + wave * 128;         // kPair, INT8: the wave's scale units of two tiles
 
   // the runs of this item (first unit of each; P^K and P^V of consecutive tiles
   // follow at constant strides) and the first run of the next one
@@ -657,7 +661,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
   const unsigned char* pkp = data + (int64_t)rl.first(n_rk) * kPBytes;
   const unsigned char* pvp = data + (own_v > 0 ? (int64_t)rl.first(n_rk + 1 + (I8 ? 1 : 0)) * kPBytes : 0);
   const unsigned char* scp = data + (I8 ? (int64_t)rl.first(n_rk + 1) * kScaleUnitBytes : 0);
-  const RunStart<KD, kPBytes> pk_first(pkp, nks, nks * kPBytes, mask_lt(1, ntiles));
+  const RunStart<KD, kPBytes> pk_first(pkp, nks);
   const int lane16 = 16 * lane;
   auto ldf = [&](const unsigned char* p, int off, int wanted = -1) {  // a bf16 fragment
     return load_frag16(p, off, lane16, wanted);
@@ -709,8 +713,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
   constexpr int kRowChunks = D / 8;  // 16-byte chunks per query row
   constexpr int kQLoads = query_loads<D>();
   __bf16* qimg = wl;
-  // steps KD .. of an R^K rank tile (kPair: in the slots' second fragments)
-  constexpr bool kMoreRk = !kPair && NK > KD;
+  constexpr bool kMoreRk = NK > KD;  // steps KD .. of an R^K rank tile
   bf16x8 rk_more[kMoreRk ? KD : 1];
   {
 #pragma unroll
@@ -722,13 +725,8 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       // the previous item could not load this one's first K run (its element size may differ)
       static_for<0, KD, 1>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
-        if (n_rk > 0) {
-          fs.ks[i][0] = ldf(rkp, i * kFragBytes);
-          if constexpr (kPair) fs.ks[i][1] = ldf(rkp, (i + KD) * kFragBytes, -(int)(NK > KD));
-        } else {
-          fs.ks[i][0] = ldp(pk_first.p, pk_first.off(i));
-          if constexpr (kPair) fs.ks[i][1] = ldp(pk_first.p, pk_first.off(i) + pk_first.delta, pk_first.wanted2);
-        }
+        if (n_rk > 0) fs.ks[i] = ldf(rkp, i * kFragBytes);
+        else fs.ks[i] = ldp(pk_first.p, pk_first.off(i));
       });
     }
     // the rest of the first R^K rank tile, then the first tile's P^V
@@ -739,15 +737,14 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       constexpr int n = decltype(own_c)::value * decltype(cs_c)::value;
       static_for<0, (n < VD ? n : VD), 1>([&](auto x) { fs.vs[decltype(x)::value] = ldp(pvp, x * kPBytes); });
     });
-    if (wave == 0) rd.derive(lane);  // the runs of the block item two ahead
     lds_barrier();
+    if (wave == kWaves - 1) rd.derive(lane);  // the runs of the block item two ahead
   }
 
   auto load_pk_first = [&]() {
     static_for<0, KD, 1>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
-      fs.ks[i][0] = ldp(pk_first.p, pk_first.off(i));
-      if constexpr (kPair) fs.ks[i][1] = ldp(pk_first.p, pk_first.off(i) + pk_first.delta, pk_first.wanted2);
+      fs.ks[i] = ldp(pk_first.p, pk_first.off(i));
     });
   };
   // ---- projection: Qt[rank][col] (stored [col][rank]), once per KV head of
@@ -818,8 +815,8 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
     const int hq0 = div_by(c0 + min(lrow, cn - 1), N_g, a.N_g_inv) - g0;
     const int hq1 = div_by(c0 + min(32 + lrow, cn - 1), N_g, a.N_g_inv) - g0;
     const int nx = nh * own_k;
-    for (int x = 0; x < nx; ++x) {
-      const int hh = x / own_k, j = x - hh * own_k, rt = wave + kWaves * j;
+    for (int x = 0, hh = 0, j = 0; x < nx; ++x) {
+      const int rt = wave + kWaves * j;
       // each step's slot is reloaded with the same step of the next rank tile (the
       // next head's run starts nrt_k NK fragments on; past the last, P^K)
       const unsigned char* after = rkp + (j + 1 < own_k ? (int64_t)hh * nrt_k + j + 1 : (int64_t)(hh + 1) * nrt_k) * NK * kFragBytes;
@@ -827,20 +824,15 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       f32x16 acc0 = zero16(), acc1 = zero16();
       static_for<0, NK, 1>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        if constexpr (k >= KD && !kPair) {
+        if constexpr (k >= KD) {
           acc0 = mfma32(rk_more[k - KD], qf[k][0], acc0);
           acc1 = mfma32(rk_more[k - KD], qf[k][1], acc1);
           rk_more[k - KD] = ldf(after, k * kFragBytes, mask_lt(x + 1, nx));
         } else {
-          constexpr int i = k % KD, u = k / KD;
-          acc0 = mfma32(fs.ks[i][u], qf[k][0], acc0);
-          acc1 = mfma32(fs.ks[i][u], qf[k][1], acc1);
-          const int pk_off = pk_first.off(i) + (u ? pk_first.delta : 0), pk_wanted = u ? pk_first.wanted2 : -1;
-          fs.ks[i][u] = ldf(to_pk ? pk_first.p : after, to_pk ? pk_off : k * kFragBytes,
-                            to_pk ? pk_wanted : mask_lt(x + 1, nx));
-          // one round of R^K: the second fragments are P^K's alone
-          if constexpr (kPair && NK == KD)
-            fs.ks[i][1] = ldf(pk_first.p, pk_first.off(i) + pk_first.delta, to_pk ? pk_first.wanted2 : 0);
+          acc0 = mfma32(fs.ks[k], qf[k][0], acc0);
+          acc1 = mfma32(fs.ks[k], qf[k][1], acc1);
+          fs.ks[k] = ldf(to_pk ? pk_first.p : after, to_pk ? pk_first.off(k) : k * kFragBytes,
+                         to_pk ? -1 : mask_lt(x + 1, nx));
         }
       });
 #pragma unroll
@@ -855,6 +847,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
         if (hq0 == hh) *reinterpret_cast<bf16x4*>(qt + lrow * qsd + r) = v0;
         if (hq1 == hh) *reinterpret_cast<bf16x4*>(qt + (32 + lrow) * qsd + r) = v1;
       }
+      if (++j == own_k) j = 0, ++hh;
     }
     if constexpr (I8) load_pk_first();
   }
@@ -878,6 +871,19 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
   const int nk_v = bm.rv_pad >> 5;
   const unsigned char* rvp = data + rv_frag(bm, D, g0, ds0, 0) * kFragBytes;
   bf16x8 rv[kRvSteps][2];
+  // its first round: a slice's steps past the ranks lie past the end of its
+  // buffer and are not read
+  auto load_rv_first = [&]() {
+    const int end = nk_v * kFragBytes;
+    const int end2 = narrow ? max(end - kRvSteps * kFragBytes, 0) : end;
+    const __amdgpu_buffer_rsrc_t r0 = frag_buffer(rvp, end);
+    const __amdgpu_buffer_rsrc_t r1 = frag_buffer(rvp + (narrow ? kRvSteps : nk_v) * kFragBytes, end2);
+    static_for<0, kRvSteps, 1>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      rv[i][0] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r0, lane16 + i * kFragBytes, 0, 0));
+      rv[i][1] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r1, lane16 + i * kFragBytes, 0, 0));
+    });
+  };
   auto tiles = [&](auto own_c, auto cs_c, auto dense_c) {
     constexpr int OWN = decltype(own_c)::value, CS = decltype(cs_c)::value;
     constexpr bool DENSE = decltype(dense_c)::value;
@@ -889,75 +895,55 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
     // carries it); applied in the column maximum and the weights' exponent
     const float sscale = DENSE && a.qscale != 0.f ? fabsf(a.qscale) : 1.f;
 
-    // one step of NT tiles from tile tt on
-    auto take = [&](int tt, auto nt_c) {
-      constexpr int NT = decltype(nt_c)::value;
-      const int after = tt + NT;  // the next step's first tile
-      float scale_unit[NT];       // INT8: this lane's entry of the wave's scale unit of each tile
-      if constexpr (I8) {
-#pragma unroll
-        for (int u = 0; u < NT; ++u)
-          scale_unit[u] = reinterpret_cast<const float*>(scp + (int64_t)(tt + u) * kWaves * kScaleUnitBytes)[lane];
-      }
-      // rank step k (P^K sub-tiles, or rebuilt keys) times the two column halves
+    for (int tt = 0; tt < ntiles; ++tt) {
+      const int after = tt + 1;
+      float scale_unit = 0.f;  // INT8: this lane's entry of the wave's scale unit
+      if constexpr (I8) scale_unit = reinterpret_cast<const float*>(scp + (int64_t)tt * kWaves * kScaleUnitBytes)[lane];
+      // rank step k (P^K sub-tile, or rebuilt keys) times the two column halves
       // of Qt; dense items multiply fp16 operands.  The next K run: the next
-      // tiles', then the next item's first (INT8: loaded by that item)
-      f32x16 sc[NT][2];
-#pragma unroll
-      for (int u = 0; u < NT; ++u) sc[u][0] = sc[u][1] = zero16();
+      // tile's, then the next item's first (INT8: loaded by that item)
+      f32x16 sc[2] = {zero16(), zero16()};
       {
         const int ln = opaque(lane);
         const __bf16* qr0 = qt + (ln & 31) * qsd + 8 * (ln >> 5);
         const __bf16* qr1 = qr0 + 32 * qsd;
         const unsigned char* kb = pkp + (int64_t)tt * nks * kPBytes;
-        RunStart<KD, kPBytes> kn(kb + (int64_t)NT * nks * kPBytes, nks, nks * kPBytes, mask_lt(after + 1, ntiles));
+        RunStart<KD, kPBytes> kn(kb + (int64_t)nks * kPBytes, nks);
         if (after >= ntiles) {
-          kn.wanted = kn.wanted2 = 0;
+          kn.wanted = 0;
           if constexpr (!I8)
-            if (next_item) kn = item_first_run<D, MAX_RT>(next_item, wave, data + (int64_t)rl.next_first() * kPBytes);
+            if (next_item) kn = item_first_run<D>(next_item, wave, data + (int64_t)rl.next_first() * kPBytes);
         }
         auto use = [&](int f, auto slot) {
           constexpr int i = decltype(slot)::value;
           const bf16x8 b0 = ld_bf16x8(qr0 + 16 * f + 16 * i), b1 = ld_bf16x8(qr1 + 16 * f + 16 * i);
-          static_for<0, NT, 1>([&](auto uc) {
-            constexpr int u = decltype(uc)::value;
-            const bf16x8 ak = use_p(fs.ks[i][u]);
-            sc[u][0] = DENSE ? mfma32_f16(ak, b0, sc[u][0]) : mfma32(ak, b0, sc[u][0]);
-            sc[u][1] = DENSE ? mfma32_f16(ak, b1, sc[u][1]) : mfma32(ak, b1, sc[u][1]);
-          });
+          const bf16x8 ak = use_p(fs.ks[i]);
+          sc[0] = DENSE ? mfma32_f16(ak, b0, sc[0]) : mfma32(ak, b0, sc[0]);
+          sc[1] = DENSE ? mfma32_f16(ak, b1, sc[1]) : mfma32(ak, b1, sc[1]);
         };
-        consume_run(kb, nks, nks * kPBytes, NT == 2 ? -1 : 0, kn, use,
-                    [&](auto slot, const unsigned char* q, int off, int wanted, int delta, int wanted2) {
-                      constexpr int i = decltype(slot)::value;
-                      fs.ks[i][0] = ldp(q, off, wanted);
-                      if constexpr (kPair) fs.ks[i][1] = ldp(q, off + delta, wanted2);
-                    });
+        consume_run(kb, nks, kn, use, [&](auto slot, const unsigned char* q, int off, int wanted) {
+          fs.ks[decltype(slot)::value] = ldp(q, off, wanted);
+        });
       }
       const int ln = opaque(lane), lrow = ln & 31, lhi = ln >> 5;
       // INT8 P factors: the scores of int8 codes times each token's K scale (lane:
       // tokens 8 j + 4 lhi + v of the wave's 32, j, v = 0..3); the V scales fold
-      // into the weights below.  The units are spread through LDS: without pairs
-      // through the wave's own maxima row, which nobody reads before the maxima
-      // below are in it
+      // into the weights below.  The unit is spread through the wave's own maxima
+      // row, which nobody reads before the maxima below are in it
       float vsc[16];
       if constexpr (I8) {
-        float* su = kPair ? units : red + wave * kCols;
+        float* su = red + wave * kCols;
+        su[ln] = scale_unit;
 #pragma unroll
-        for (int u = 0; u < NT; ++u) {
-          su[64 * u + ln] = scale_unit[u];
+        for (int j = 0; j < 4; ++j) {
+          const float4 k4 = *reinterpret_cast<const float4*>(su + 8 * j + 4 * lhi);
+          const float4 v4 = *reinterpret_cast<const float4*>(su + 32 + 8 * j + 4 * lhi);
+          const float kk[4] = {k4.x, k4.y, k4.z, k4.w};
+          vsc[4 * j] = v4.x, vsc[4 * j + 1] = v4.y, vsc[4 * j + 2] = v4.z, vsc[4 * j + 3] = v4.w;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float4 k4 = *reinterpret_cast<const float4*>(su + 64 * u + 8 * j + 4 * lhi);
-            const float kk[4] = {k4.x, k4.y, k4.z, k4.w};
-            if constexpr (!kPair) {
-              const float4 v4 = *reinterpret_cast<const float4*>(su + 32 + 8 * j + 4 * lhi);
-              vsc[4 * j] = v4.x, vsc[4 * j + 1] = v4.y, vsc[4 * j + 2] = v4.z, vsc[4 * j + 3] = v4.w;
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              sc[u][0][4 * j + v] *= kk[v];
-              sc[u][1][4 * j + v] *= kk[v];
-            }
+          for (int v = 0; v < 4; ++v) {
+            sc[0][4 * j + v] *= kk[v];
+            sc[1][4 * j + v] *= kk[v];
           }
         }
       }
@@ -965,23 +951,20 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       // hold any; the test is wave-uniform), and for a prefill chunk's shared
       // tail the tokens past each column's causal limit; wave-local column max
       float mx[2] = {-INFINITY, -INFINITY};
-#pragma unroll
-      for (int u = 0; u < NT; ++u) {
-        const int tw = (tile0 + tt + u) * kTile + wave * kTokWave;
-        if (tw + kTokWave > T || (DENSE && causal && tw + kTokWave > lim_min)) {
-#pragma unroll
-          for (int ch = 0; ch < 2; ++ch)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int tok = tw + 8 * (v >> 2) + 4 * lhi + (v & 3);
-              if (tok >= T || (DENSE && tok >= lim[ch])) sc[u][ch][v] = -INFINITY;
-            }
-        }
+      const int tw = (tile0 + tt) * kTile + wave * kTokWave;
+      if (tw + kTokWave > T || (DENSE && causal && tw + kTokWave > lim_min)) {
 #pragma unroll
         for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) mx[ch] = fmaxf(mx[ch], sc[u][ch][v]);
+          for (int v = 0; v < 16; ++v) {
+            const int tok = tw + 8 * (v >> 2) + 4 * lhi + (v & 3);
+            if (tok >= T || (DENSE && tok >= lim[ch])) sc[ch][v] = -INFINITY;
+          }
       }
+#pragma unroll
+      for (int ch = 0; ch < 2; ++ch)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mx[ch] = fmaxf(mx[ch], sc[ch][v]);
 #pragma unroll
       for (int ch = 0; ch < 2; ++ch) {
         mx[ch] = fmaxf(mx[ch], __shfl_xor(mx[ch], 32)) * sscale;
@@ -991,10 +974,10 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       // The gang's workgroups read the same P at the same time, so what they have
       // in flight from HBM together is only one workgroup's: each fetches its share
       // of the wave's coming fragments (this tile's P^V, then the next one's P^K,
-      // in 64 lines of 128 bytes) into the XCD's L2.  Issued here no younger load
-      // is needed before the value pass' second round, so the fetch, whose value is
-      // never used, holds nobody up (loads return in order).  Not with pairs: their
-      // steps leave no register for it
+      // in 64 lines of 128 bytes) into the XCD's L2.  Loads return in order, so the
+      // value pass' first fragments past the slots (vx below) wait for the fetch
+      // too; issued after that pass it came too late to help.  Dense items of one
+      // gang read different K and V and fetch nothing
       uint32_t touched[kTouches > 0 ? kTouches : 1];
       if constexpr (kTouches > 0) {
         const int lane128 = 128 * opaque(lane);
@@ -1007,7 +990,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
           const int at = (k_part ? c - v_chunks : c) * 8192;
           const unsigned char* base = k_part ? pkp + (int64_t)after * nks * kPBytes : pvp + (int64_t)tt * 16 * OWN * kPBytes;
           // an empty buffer past the part's end, and for a gang of one
-          const int bytes = a.gang > 1 ? max(0, min(8192, (k_part ? k_lines : v_lines) * 128 - at)) : 0;
+          const int bytes = !DENSE && a.gang > 1 ? max(0, min(8192, (k_part ? k_lines : v_lines) * 128 - at)) : 0;
           const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
               const_cast<unsigned char*>(base) + at, 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
           touched[l] = __builtin_amdgcn_raw_buffer_load_b32(r, lane128, 0, 0);
@@ -1031,23 +1014,17 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
         float lsum = 0.f;
         const float mref = m_run[ch] == -INFINITY ? 0.f : m_run[ch];
 #pragma unroll
-        for (int u = 0; u < NT; ++u)
+        for (int j = 0; j < 4; ++j) {
+          bf16x4 wv;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if constexpr (I8 && kPair) {
-              const float4 v4 = *reinterpret_cast<const float4*>(units + 64 * u + 32 + 8 * j + 4 * lhi);
-              vsc[4 * j] = v4.x, vsc[4 * j + 1] = v4.y, vsc[4 * j + 2] = v4.z, vsc[4 * j + 3] = v4.w;
-            }
-            bf16x4 wv;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const float w = fast_exp2(fmaf(sc[u][ch][4 * j + v], sscale, -mref));
-              lsum += w;
-              if constexpr (I8) wv[v] = (__bf16)(w * vsc[4 * j + v]);
-              else wv[v] = (__bf16)w;
-            }
-            *reinterpret_cast<bf16x4*>(wl + (32 * ch + lrow) * kWS + u * kTile + wave * kTokWave + 8 * j + 4 * lhi) = wv;
+          for (int v = 0; v < 4; ++v) {
+            const float w = fast_exp2(fmaf(sc[ch][4 * j + v], sscale, -mref));
+            lsum += w;
+            if constexpr (I8) wv[v] = (__bf16)(w * vsc[4 * j + v]);
+            else wv[v] = (__bf16)w;
           }
+          *reinterpret_cast<bf16x4*>(wl + (32 * ch + lrow) * kWS + wave * kTokWave + 8 * j + 4 * lhi) = wv;
+        }
         l_run[ch] = l_run[ch] * alpha[ch] + lsum;
         // summed here: left to itself the compiler keeps all the weights to sum them later
         asm volatile("" : "+v"(l_run[ch]));
@@ -1072,52 +1049,40 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
           }
         }
         const int steps = OWN > 2 ? 16 : nst;  // a whole number of rounds
+        // weight operand rows of the wave's segment (relative step st at 16 st)
+        const __bf16* wr0 = wl + lrow * kWS + 8 * lhi + 16 * nst * sg;
+        const __bf16* wr1 = wr0 + 32 * kWS;
 #pragma clang loop unroll(disable)
-        for (int u = 0; u < NT; ++u) {
-          // weight operand rows of the wave's segment (relative step st at 16 st)
-          const __bf16* wr0 = wl + lrow * kWS + 8 * lhi + u * kTile + 16 * nst * sg;
-          const __bf16* wr1 = wr0 + 32 * kWS;
-          const unsigned char* vu = vb + u * 16 * OWN * kPBytes;
-#pragma clang loop unroll(disable)
-          for (int st = 0; st < steps; st += CS) {
-            const int in_step = mask_lt(st + CS, steps) | mask_lt(u + 1, NT);
-            const int wanted = in_step | mask_lt(after, ntiles);
-            const int on = (st + CS >= steps ? 16 : st + CS) * OWN * kPBytes;
-            static_for<0, CS, 1>([&](auto ic) {
-              constexpr int i = decltype(ic)::value;
-              const bf16x8 w0 = ld_bf16x8(wr0 + 16 * st + 16 * i), w1 = ld_bf16x8(wr1 + 16 * st + 16 * i);
-              static_for<0, OWN, 1>([&](auto rc) {
-                constexpr int r = decltype(rc)::value, x = i * OWN + r;
-                bf16x8& slot = [&]() -> bf16x8& {
-                  if constexpr (x < VD) return fs.vs[x];
-                  else return vx[x - VD];
-                }();
-                const bf16x8 pa = use_p(slot);
-                oacc[r][0] = mfma32(pa, w0, oacc[r][0]);
-                oacc[r][1] = mfma32(pa, w1, oacc[r][1]);
-                slot = ldp(vu, on + x * kPBytes, x < VD ? wanted : in_step);
-              });
+        for (int st = 0; st < steps; st += CS) {
+          const int in_step = mask_lt(st + CS, steps);
+          const int wanted = in_step | mask_lt(after, ntiles);
+          const int on = (st + CS >= steps ? 16 : st + CS) * OWN * kPBytes;
+          static_for<0, CS, 1>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const bf16x8 w0 = ld_bf16x8(wr0 + 16 * st + 16 * i), w1 = ld_bf16x8(wr1 + 16 * st + 16 * i);
+            static_for<0, OWN, 1>([&](auto rc) {
+              constexpr int r = decltype(rc)::value, x = i * OWN + r;
+              bf16x8& slot = [&]() -> bf16x8& {
+                if constexpr (x < VD) return fs.vs[x];
+                else return vx[x - VD];
+              }();
+              const bf16x8 pa = use_p(slot);
+              oacc[r][0] = mfma32(pa, w0, oacc[r][0]);
+              oacc[r][1] = mfma32(pa, w1, oacc[r][1]);
+              slot = ldp(vb, on + x * kPBytes, x < VD ? wanted : in_step);
+              pin_load();
             });
-          }
+          });
         }
       } else {
         lds_barrier();
       }
 #pragma unroll
       for (int l = 0; l < kTouches; ++l) asm volatile("" ::"v"(touched[l]));
-    };
-    int tt = 0;
-    if constexpr (kPair)
-      for (; tt + 1 < ntiles; tt += 2) take(tt, std::integral_constant<int, 2>{});
-    for (; tt < ntiles; ++tt) take(tt, std::integral_constant<int, 1>{});
+    }
 
     // the up-projection's first R^V steps load while the partials are combined
-    if constexpr (!DENSE)
-      static_for<0, kRvSteps, 1>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        rv[i][0] = ldf(rvp, i * kFragBytes, mask_lt(i, nk_v));
-        rv[i][1] = ldf(rvp, ((narrow ? kRvSteps : nk_v) + i) * kFragBytes, mask_lt(narrow ? i + kRvSteps : i, nk_v));
-      });
+    if constexpr (!DENSE) load_rv_first();
     const int ln = opaque(lane), lrow = ln & 31, lhi = ln >> 5;
 #pragma unroll
     for (int ch = 0; ch < 2; ++ch) l_run[ch] += __shfl_xor(l_run[ch], 32);
@@ -1128,7 +1093,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
     // fp32): the waves of segments [h, 2h) hand theirs to segments [0, h)
     if (nseg > 1) {
       float4* segbuf = reinterpret_cast<float4*>(smem);  // [slot][owned tile][ch][4][64 lanes]
-      const int own_max = (nrt_v + ng - 1) / ng;        // slot size: the largest rank group's tiles
+      const int own_max = (nrt_v + ng - 1) >> lg_ng;    // slot size: the largest rank group's tiles
       for (int h = nseg / 2; h >= 1; h /= 2) {
         if (sg >= h && sg < 2 * h) {
           float4* dst = segbuf + ((sg - h) * ng + rg) * own_max * 2 * 4 * 64 + ln;
@@ -1206,27 +1171,15 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
 
   // ---- up-projection through R^V and the partial (m, l, o) ----
   const int ln = opaque(lane);
-  constexpr int NCB = NDS / 4;               // 16-column blocks per wave
+  constexpr int NCB = up_col_blocks<D>();
+  constexpr bool kFold = MAX_RT == 2;  // (plans of more rank tiles per wave do not)
   const int cb0 = wave / (narrow ? NDS : NDS / 2) * NCB;  // the first of them
   // this thread's output dims of its columns in the slot
-  int64_t colg[NCB];
-#pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) colg[cb] = query_row(a, c0 + min(16 * (cb0 + cb) + (ln & 15), cn - 1));
   auto slot_o = [&](int cb, int sl) {
-    return reinterpret_cast<float4*>(a.part_o + (colg[cb] * a.n_slots + slot) * D + 16 * (ds0 + sl) +
-                                     4 * (ln >> 4));
+    const int64_t row = query_row(a, c0 + min(16 * (cb0 + cb) + (ln & 15), cn - 1));
+    return reinterpret_cast<float4*>(a.part_o + (row * a.n_slots + slot) * D + 16 * (ds0 + sl) + 4 * (ln >> 4));
   };
-  // loads that the end of the item and the next one wait for: the group's
-  // running output, the next item's queries
-  const bool first = (it.flags & kItemFirst) != 0;
-  float4 old[NCB][2];
-  if (!first) {
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-      old[cb][0] = *slot_o(cb, 0);
-      if (!narrow) old[cb][1] = *slot_o(cb, 1);
-    }
-  }
+  // the next item's queries
   if (next_item) {
     const int nc0 = __builtin_amdgcn_readfirstlane(next_item->req), nf = __builtin_amdgcn_readfirstlane(next_item->flags);
     load_queries<D>(a, nc0, ((nf >> kItemColsShift) & 63) + 1, tid, qv);
@@ -1311,6 +1264,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
   }
   {
     // fold into the group's running partial (log-sum-exp)
+    const bool first = !kFold || (it.flags & kItemFirst) != 0;
     float fa[2], fb[2];
 #pragma unroll
     for (int ch = 0; ch < 2; ++ch) {
@@ -1328,12 +1282,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
 #pragma unroll
       for (int sl = 0; sl < 2; ++sl) {
         uacc[cb][sl] *= sb;
-        if (!first) {
-          uacc[cb][sl][0] += old[cb][sl].x * sa;
-          uacc[cb][sl][1] += old[cb][sl].y * sa;
-          uacc[cb][sl][2] += old[cb][sl].z * sa;
-          uacc[cb][sl][3] += old[cb][sl].w * sa;
-        }
+        if constexpr (kFold) acc.o[cb][sl] = uacc[cb][sl] = first ? uacc[cb][sl] : acc.o[cb][sl] * sa + uacc[cb][sl];
       }
     }
     if (tid < kCols) {
@@ -1341,13 +1290,15 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       acc.l = first ? l_item * fb[ch] : acc.l * fa[ch] + l_item * fb[ch];
     }
   }
+  if (!kFold || (it.flags & kItemFlush)) {
 #pragma unroll
-  for (int cb = 0; cb < NCB; ++cb)
-    if (16 * (cb0 + cb) + (ln & 15) < cn) {
+    for (int cb = 0; cb < NCB; ++cb)
+      if (16 * (cb0 + cb) + (ln & 15) < cn) {
 #pragma unroll
-      for (int sl = 0; sl < (narrow ? 1 : 2); ++sl)
-        *slot_o(cb, sl) = make_float4(uacc[cb][sl][0], uacc[cb][sl][1], uacc[cb][sl][2], uacc[cb][sl][3]);
-    }
+        for (int sl = 0; sl < (narrow ? 1 : 2); ++sl)
+          *slot_o(cb, sl) = make_float4(uacc[cb][sl][0], uacc[cb][sl][1], uacc[cb][sl][2], uacc[cb][sl][3]);
+      }
+  }
   if ((it.flags & kItemFlush) && tid < cn) {
     const int64_t colg = query_row(a, c0 + tid);
     a.part_ml[colg * a.n_slots + slot] = make_float2(tid < 32 ? acc.m[0] : acc.m[1], acc.l);
@@ -1355,7 +1306,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
   rl.advance();
 }
 
-template <int D, int MAX_RT, int MODE>
+template <int D, int MAX_RT, bool FETCH, int MODE>
 __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const WgProgram p = a.wg[blockIdx.x];
@@ -1368,8 +1319,8 @@ __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
   lds_barrier();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned char* work = smem + a.prog_bytes;
-  Streams<D, MAX_RT> fs;
-  GroupAcc acc;
+  Streams<D> fs;
+  GroupAcc<up_col_blocks<D>()> acc;
   RunDeriver<D> rd;
   rd.items = smem;
   rd.n_items = p.n_items;
@@ -1378,7 +1329,7 @@ __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
   rd.rbuf = reinterpret_cast<int2*>(smem + (size_t)p.n_items * sizeof(WorkItem));
   rd.recon_delta = a.recon_delta;
   rd.run_cap = a.run_cap;
-  if (wave == 0) {
+  if (wave == kWaves - 1) {
     rd.derive(threadIdx.x & 63);
     rd.derive(threadIdx.x & 63);
   }
@@ -1388,7 +1339,22 @@ __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
   rl.run_cap = a.run_cap;
   rl.rb = 0;
   bf16x8 qv[query_loads<D>()];
-  bool primed = false;
+  // the first block item's queries and first K run load while the tail items,
+  // which come before it, run
+  if (p.first_block < p.n_items) {
+    const WorkItem* it = reinterpret_cast<const WorkItem*>(smem) + p.first_block;
+    const int c0 = __builtin_amdgcn_readfirstlane(it->req), fl = __builtin_amdgcn_readfirstlane(it->flags);
+    load_queries<D>(a, c0, ((fl >> kItemColsShift) & 63) + 1, threadIdx.x, qv);
+    if constexpr (MODE != 1) {  // INT8 items load their first K run themselves
+      const int lane16 = 16 * (threadIdx.x & 63);
+      const auto run = item_first_run<D>(it, wave, reinterpret_cast<const unsigned char*>(a.data) +
+                                                       (int64_t)rl.first(0) * kFragElems * 2);
+      static_for<0, Streams<D>::KD, 1>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        fs.ks[i] = load_frag16(run.p, run.off(i), lane16);
+      });
+    }
+  }
   for (int k = 0; k < p.n_items; ++k) {
     const WorkItem it = lds_item(smem + (size_t)k * sizeof(WorkItem));
     if (k > 0) lds_barrier();  // the previous item's LDS reads are done
@@ -1397,23 +1363,8 @@ __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     if (it.kind == kItemBlock) {
-      if (!primed) {  // the first block item (block items follow the tail items)
-        load_queries<D>(a, it.req, ((it.flags >> kItemColsShift) & 63) + 1, tid, qv);
-        if constexpr (MODE != 1) {  // INT8 items load their first K run themselves
-          const auto run = item_first_run<D, MAX_RT>(reinterpret_cast<const WorkItem*>(smem) + k, wave,
-                                                     reinterpret_cast<const unsigned char*>(a.data) +
-                                                         (int64_t)rl.first(0) * kFragElems * 2);
-          static_for<0, Streams<D, MAX_RT>::KD, 1>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            fs.ks[i][0] = load_frag16(run.p, run.off(i), 16 * (tid & 63));
-            if constexpr (Streams<D, MAX_RT>::kPair)
-              fs.ks[i][1] = load_frag16(run.p, run.off(i) + run.delta, 16 * (tid & 63), run.wanted2);
-          });
-        }
-        primed = true;
-      }
       const WorkItem* next = k + 1 < p.n_items ? reinterpret_cast<const WorkItem*>(smem) + k + 1 : nullptr;
-      block_item<D, MAX_RT, MODE>(a, it, work, fs, rl, rd, acc, qv, next, tid);
+      block_item<D, MAX_RT, FETCH, MODE>(a, it, work, fs, rl, rd, acc, qv, next, tid);
     } else if (it.kind == kItemTail) {
       tail_item<D>(a, it, work, tid);
     }
@@ -1542,44 +1493,47 @@ hipError_t launch_scale_units(const float* ks, const float* vs, int T_pad, float
 }
 
 
-template <int D, int MAX_RT, int MODE>
+template <int D, int MAX_RT, bool FETCH, int MODE>
 static hipError_t launch_attend_t(const AttendArgs& a, int grid, size_t lds, hipStream_t s, hipEvent_t e0,
                                   hipEvent_t e1) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_kernel<D, MAX_RT, MODE>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_kernel<D, MAX_RT, FETCH, MODE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipExtLaunchKernelGGL((attend_kernel<D, MAX_RT, MODE>), dim3(grid), dim3(kThreads), (uint32_t)lds, s, e0, e1, 0, a);
+  hipExtLaunchKernelGGL((attend_kernel<D, MAX_RT, FETCH, MODE>), dim3(grid), dim3(kThreads), (uint32_t)lds, s, e0, e1, 0, a);
   return hipGetLastError();
 }
 
 template <int D, int MODE>
-static hipError_t launch_attend_d(const AttendArgs& a, int max_rt, int grid, size_t lds, hipStream_t s, hipEvent_t e0,
+static hipError_t launch_attend_d(const AttendArgs& a, int max_rt, bool fetch, int grid, size_t lds, hipStream_t s, hipEvent_t e0,
                                   hipEvent_t e1) {
   switch (max_rt) {
-    case 2: return launch_attend_t<D, 2, MODE>(a, grid, lds, s, e0, e1);
-    case 3: return launch_attend_t<D, 3, MODE>(a, grid, lds, s, e0, e1);
-    case 4: return launch_attend_t<D, 4, MODE>(a, grid, lds, s, e0, e1);
+    case 2:
+      if constexpr (MODE != 2)
+        if (fetch) return launch_attend_t<D, 2, true, MODE>(a, grid, lds, s, e0, e1);
+      return launch_attend_t<D, 2, false, MODE>(a, grid, lds, s, e0, e1);
+    case 3: return launch_attend_t<D, 3, true, MODE>(a, grid, lds, s, e0, e1);
+    case 4: return launch_attend_t<D, 4, true, MODE>(a, grid, lds, s, e0, e1);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <int D>
-static hipError_t launch_attend_m(const AttendArgs& a, int max_rt, bool p_int8, bool gemv, int grid, size_t lds,
+static hipError_t launch_attend_m(const AttendArgs& a, int max_rt, bool fetch, bool p_int8, bool gemv, int grid, size_t lds,
                                   hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (p_int8) return launch_attend_d<D, 1>(a, max_rt, grid, lds, s, e0, e1);
-  if (gemv) return launch_attend_d<D, 2>(a, max_rt, grid, lds, s, e0, e1);
-  return launch_attend_d<D, 0>(a, max_rt, grid, lds, s, e0, e1);
+  if (p_int8) return launch_attend_d<D, 1>(a, max_rt, fetch, grid, lds, s, e0, e1);
+  if (gemv) return launch_attend_d<D, 2>(a, max_rt, fetch, grid, lds, s, e0, e1);
+  return launch_attend_d<D, 0>(a, max_rt, fetch, grid, lds, s, e0, e1);
 }
 
-hipError_t launch_attend(const AttendArgs& a, int head_dim, int max_rt, bool p_int8, bool gemv, int grid,
+hipError_t launch_attend(const AttendArgs& a, int head_dim, int max_rt, bool fetch, bool p_int8, bool gemv, int grid,
                          size_t lds_bytes, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (grid == 0) return hipSuccess;
-  if (head_dim == 64) return launch_attend_m<64>(a, max_rt, p_int8, gemv, grid, lds_bytes, s, e0, e1);
-  if (head_dim == 128) return launch_attend_m<128>(a, max_rt, p_int8, gemv, grid, lds_bytes, s, e0, e1);
+  if (head_dim == 64) return launch_attend_m<64>(a, max_rt, fetch, p_int8, gemv, grid, lds_bytes, s, e0, e1);
+  if (head_dim == 128) return launch_attend_m<128>(a, max_rt, fetch, p_int8, gemv, grid, lds_bytes, s, e0, e1);
   return hipErrorInvalidValue;
 }
 

@@ -16,11 +16,7 @@ namespace milo {
 size_t attend_lds_base_bytes(int head_dim, int rk_pad_max, int rv_pad_max, bool half_w) {
   (void)half_w;  // no layout has halved weight tiles any more
   const size_t qsd = (size_t)rk_pad_max + 8;
-  const bool pair = rk_pad_max <= kPairRank && rv_pad_max <= kPairRank;
-  // the weights of one or two tiles, the per-wave column maxima, and with two
-  // tiles the waves' INT8 scale units
-  const size_t weights = (size_t)kCols * (pair ? kWStridePair : kWStride) * 2;
-  const size_t loop = kCols * qsd * 2 + weights + (size_t)kWaves * kCols * 4 * (pair ? 3 : 1);
+  const size_t loop = kCols * qsd * 2 + (size_t)kCols * kWStride * 2 + (size_t)kWaves * kCols * 4;
   // up-projection: the latent accumulator as bf16 [col][rank], or the segment
   // partials being combined (at most 4 slots x 3 rank tiles x 8 KiB), then the
   // per-wave column sums at the end of the region
@@ -290,6 +286,9 @@ bool build_schedule(const PlanInput& c, const int32_t* table, int n_sel, int n_q
     }
     make_jobs(best_share, parts, jobs);
   }
+  int64_t ranks = 0;
+  for (int j = 0; j < n_sel; ++j) ranks += item_meta(table[j]).rk_pad + item_meta(table[j]).rv_pad;
+  out->mean_ranks = n_sel > 0 ? (int)(ranks / n_sel) : 0;
   const int n_parts = (int)parts.size();
   out->n_parts = n_parts;
   for (const Part& pt : parts) {
@@ -342,6 +341,7 @@ bool build_schedule(const PlanInput& c, const int32_t* table, int n_sel, int n_q
       pb.resize(items.size() * sizeof(WorkItem));
       std::memcpy(pb.data(), items.data(), pb.size());
       e.n_items = (int32_t)items.size();
+      while (e.first_block < e.n_items && items[e.first_block].kind != kItemBlock) ++e.first_block;
       e.words = (int32_t)(pb.size() / 4);
       // LDS: the items, then every wave's run buffers
       max_prog = std::max(max_prog, pb.size() + run_bytes);

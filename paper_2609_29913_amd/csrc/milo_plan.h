@@ -43,6 +43,7 @@ struct Schedule {
   int n_launch = 0, n_parts = 0, prog_bytes = 0, rk_pad_max = 32, rv_pad_max = 32, max_own = 1;
   int n_block_slots = 0;  // block-group slots of the busiest column tile
   int gang = 1;           // workgroups per gang
+  int mean_ranks = 0;     // mean of the items' rk + rv (padded), block by block
   bool half_w = false;    // always false: no plan halves the weight tile any more
   int64_t count_off = 0;  // byte offset of the int32 [n_ct] slot counts in `bytes`
   int run_cap = kRunCap;  // entries of each wave's run buffers (run_cap_for of this plan's items)

@@ -157,6 +157,10 @@ static void run_case(int case_no, int n_kv, int d, int G, int n_q, int n_chunks,
     CHECK((size_t)p.words * 4 + run_bytes <= (size_t)sch.prog_bytes, "program %d exceeds its LDS region", e);
     std::vector<WorkItem> items(p.n_items);
     std::memcpy(items.data(), sch.bytes.data() + p.off, (size_t)p.n_items * sizeof(WorkItem));
+    // tail items come first, the block items start where the entry says
+    CHECK(p.first_block >= 0 && p.first_block <= p.n_items, "program %d first block item %d", e, p.first_block);
+    for (int i = 0; i < p.n_items; ++i)
+      CHECK((items[i].kind == kItemBlock) == (i >= p.first_block), "program %d item %d", e, i);
     int group_tile = -1, group_slot = -1;
     bool open = false;
     for (int i = 0; i < p.n_items; ++i) {
