@@ -194,12 +194,19 @@ int milo_attend_prefill(milo_cache* cache, const int32_t* block_table, int32_t n
  *                          attended as uncompressed keys and values.
  *   MILO_PATH_AUTO         per block and call, whichever an MI355X cost model
  *                          (fitted to measured kernel times) expects to be
- *                          faster: reconstruction pays for blocks of
- *                          high rank attended by many query columns (the
- *                          latent route costs ~ r N (T + d), reconstruction
+ *                          faster, and latent throughout unless the call as a
+ *                          whole gains: reconstruction pays for blocks of high
+ *                          rank attended by many query columns (the latent
+ *                          route costs ~ r N (T + d), reconstruction
  *                          ~ r T H_kv d + T H_kv d + N T d; N = n_q H_q), e.g.
- *                          the ranks of 768 of a 14B-shaped 64-query step.
- * Both routes compute the same attention up to rounding.  A plan with any
+ *                          none of a 14B-shaped 64-query step, the ranks from
+ *                          ~200 on of a 256-query one.
+ * Both routes compute the same attention up to rounding, but not equally: rebuilt
+ * keys are fp16 and meet the unscaled query, the latent route rounds the projected
+ * query to bf16.  Relative error against 64 bits on the 14B-shaped step 2.2e-3 rebuilt,
+ * 2.8e-3 latent, more apart under a sharper softmax.  A caller who wants the
+ * rebuilt route's precision asks for MILO_PATH_RECONSTRUCT; AUTO goes by time alone.
+ * A plan with any
  * reconstructed block cuts the query columns per KV head.  INT8 caches attend
  * latent only (UNSUPPORTED for the other paths), and so does
  * milo_attend_decode_noalloc (AUTO attends latent there; RECONSTRUCT returns

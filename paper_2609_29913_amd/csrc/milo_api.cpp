@@ -614,26 +614,6 @@ class CacheWorkspace : public Workspace {
   milo_cache* c_;
 };
 
-// Reconstruct-then-attend pays for a block when rebuilding its keys and values
-// and attending them densely is faster than the latent route.  Per-block times
-// (microseconds) fitted to MI355X kernel timings of the 7B- (28-layer) and
-// 14B-shaped steps, for a block of T tokens, ranks rk / rv, N query columns,
-// D = H_kv d:
-//   latent        2.65e-9 N (rk + rv)(T + d)        (latent block items)
-//   reconstruct   4.17e-9 T D (rk + rv)             (reconstruction GEMMs)
-//               + 1.99e-6 T D                       (writing, then reading, the 16-bit K and V)
-//               + 7.06e-9 N T d                     (dense block items)
-// and reconstruction is chosen below 0.95 of the latent time: in the 14B-shaped
-// 64-query step the ranks of 768 alone.  (Before fragments streamed through
-// registers the latent constant was 4.24e-9 and every rank from 448 on was
-// rebuilt; that choice now takes 2056 us where the latent route takes 1783.)
-bool recon_pays(int T, int rk, int rv, int64_t N, int D, int d) {
-  const double r = (double)rk + rv;
-  const double lat = 2.65e-9 * (double)N * r * (T + d);
-  const double rec = 4.17e-9 * (double)T * D * r + 1.99e-6 * (double)T * D + 7.06e-9 * (double)N * T * d;
-  return rec < 0.95 * lat;
-}
-
 }  // namespace
 
 namespace milo {
@@ -696,12 +676,11 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
     if (must && !ws.can_recon())
       return fail(MILO_ERR_UNSUPPORTED, "block %d has rank above %d and needs reconstruction, which this entry point "
                   "does not do", b, kMaxRank);
-    if (must || rope) recon[j] = 1;
-    else if (c->path != MILO_PATH_LATENT && ws.can_recon())
-      recon[j] = c->path == MILO_PATH_RECONSTRUCT ||
-                 recon_pays(c->T[b], c->rk[b], c->rv[b], (int64_t)n_q * n_q_heads, c->n_kv * c->d, c->d);
-    n_recon += recon[j];
+    recon[j] = must || rope || (c->path == MILO_PATH_RECONSTRUCT && ws.can_recon());
   }
+  if (c->path == MILO_PATH_AUTO && ws.can_recon())
+    choose_rebuilt(c->meta.data(), block_table, n_sel, (int64_t)n_q * n_q_heads, c->n_kv * c->d, c->d, recon.data());
+  for (int j = 0; j < n_sel; ++j) n_recon += recon[j];
 
   // ---- the latent projection: MFMA (measured faster on gfx950 at every batch,
   // 7 columns per KV head included), or a wavefront GEMV kernel variant for

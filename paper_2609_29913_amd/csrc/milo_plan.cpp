@@ -416,6 +416,45 @@ bool build_schedule(const PlanInput& c, const int32_t* table, int n_sel, int n_q
   return false;
 }
 
+// Reconstruct-then-attend pays for a block when rebuilding its keys and values and
+// attending them densely is faster than the latent route.  Times per block
+// (microseconds), a least-squares fit of both routes on an MI355X: 96 blocks of 1024
+// tokens, d = 64 and 128, D = 128 / 512 / 1024, ranks 64 .. 896, 896 .. 12800 columns
+// (rebuilding within 5% at d = 128, the latent route within 10% from 2560 columns on):
+//   latent        1.84e-9 N (rk + rv)(T + d) + 6.6e-7 N T
+//   reconstruct   4.27e-9 T D (rk + rv)            (reconstruction GEMMs)
+//               + 1.91e-6 T D                      (writing, then reading, the 16-bit K and V)
+//               + (1.31e-9 d + 7.8e-7) N T         (dense block items)
+// The call as a whole has to gain too: one with any rebuilt block waits for the
+// reconstruction kernel and cuts its columns per KV head, which measured about
+// 30 us (one of six blocks rebuilt, 2560 columns: 60 us latent, 98 mixed).
+// Measured, latent / every block rebuilt / this rule's choice: 14B layer of 96 blocks
+// of rank 768, 64 requests 986 / 1079 / latent; 160 requests 2368 / 1465 / rebuilt;
+// ranks 128 .. 768, 256 requests 2441 / 1591 / 86 of 96 rebuilt; 7B prefill of 256
+// tokens, ranks 64 .. 512 1211 / 892 / 81 rebuilt.
+constexpr double kRouteMargin = 0.95, kRouteCallMargin = 0.97, kRouteCallCost = 30.0;
+void choose_rebuilt(const BlockMeta* meta, const int32_t* table, int n_sel, int64_t N, int D, int d, char* recon) {
+  double latent = 0.0, chosen = 0.0;  // of the blocks not rebuilt already
+  bool any = false;                   // the call pays for rebuilding already
+  std::vector<int> pick;
+  for (int j = 0; j < n_sel; ++j) {
+    if (recon[j]) {
+      any = true;
+      continue;
+    }
+    const BlockMeta& m = meta[table[j]];
+    const double r = (double)m.rk_pad + m.rv_pad, T = m.T, n = (double)N;
+    const double lat = 1.84e-9 * n * r * (T + d) + 6.6e-7 * n * T;
+    const double rec = 4.27e-9 * T * D * r + 1.91e-6 * T * D + (1.31e-9 * d + 7.8e-7) * n * T;
+    const bool pays = rec < kRouteMargin * lat;
+    if (pays) pick.push_back(j);
+    latent += lat;
+    chosen += pays ? rec : lat;
+  }
+  if (!any && chosen + kRouteCallCost >= kRouteCallMargin * latent) return;
+  for (int j : pick) recon[j] = 1;
+}
+
 void build_recon_plan(const BlockMeta* meta, const int32_t* table, int n_sel, const char* recon, int n_kv, int d,
                       std::vector<int64_t>* region, ReconPlan* out, const int32_t* rope_pos) {
   out->blocks.clear();

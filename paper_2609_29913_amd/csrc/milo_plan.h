@@ -68,6 +68,11 @@ struct ReconPlan {
 void build_recon_plan(const BlockMeta* meta, const int32_t* table, int n_sel, const char* recon, int n_kv, int d,
                       std::vector<int64_t>* region, ReconPlan* out, const int32_t* rope_pos = nullptr);
 
+// The automatic route: which of the selected blocks table[0 .. n_sel) a call of N
+// query columns rebuilds (recon[j] = 1), besides those that recon already names.
+// D = H_kv d.
+void choose_rebuilt(const BlockMeta* meta, const int32_t* table, int n_sel, int64_t N, int D, int d, char* recon);
+
 // Build the plan for the selected blocks table[0 .. n_sel), n_q requests with
 // n_chunks planned tail chunks each, over the column tiles `til`.  program_cap
 // (< 0: none) caps the LDS bytes of a workgroup program.  Returns false with a

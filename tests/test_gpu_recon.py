@@ -66,9 +66,10 @@ def test_reconstruct_random_shapes(seed):
 
 
 def _mixed_problem():
-    # 14B-shaped heads (2560 columns): high-rank blocks pay for reconstruction, low-rank ones do not
+    # 14B-shaped heads (12800 columns): high-rank blocks pay for reconstruction, low-rank ones
+    # do not (at 64 requests no block does: 60 us latent, 98 with one rebuilt)
     return synth.make_problem(77, [1024, 1024, 700, 1024, 300, 1024], [768, 128, 640, 128, 160, 512],
-                              [768, 96, 640, 128, 128, 576], n_kv_heads=8, head_dim=128, n_q=64, n_q_heads=40,
+                              [768, 96, 640, 128, 128, 576], n_kv_heads=8, head_dim=128, n_q=320, n_q_heads=40,
                               tail_cap=100)
 
 
