@@ -268,7 +268,7 @@ int milo_cache_create(const milo_cache_desc* desc, const uint16_t* const* pk, co
   };
   hipError_t e = hipGetDevice(&c->device);
   if (e != hipSuccess) { c->device = -1; return cleanup_fail(hip_fail(e, "hipGetDevice")); }
-  if ((e = hipMalloc(&c->data, (size_t)c->data_elems * 2 + kOverread)) != hipSuccess)
+  if ((e = hipMalloc(&c->data, (size_t)c->data_elems * 2)) != hipSuccess)
     return cleanup_fail(hip_fail(e, "hipMalloc(packed factors)"));
   if (!src_on_device && (e = hipMalloc(&staging, (size_t)stage_elems * 2)) != hipSuccess)
     return cleanup_fail(hip_fail(e, "hipMalloc(staging)"));
@@ -599,7 +599,7 @@ class CacheWorkspace : public Workspace {
       if (cap >= 0 && c->data_elems * 2 + bytes > cap)
         return fail(MILO_ERR_OUT_OF_MEMORY, "reconstruction buffer of %lld bytes exceeds MILO_MAX_DEVICE_BYTES",
                     (long long)bytes);
-      MILO_HIP(hipMalloc(&c->recon_raw, (size_t)bytes + kOverread));
+      MILO_HIP(hipMalloc(&c->recon_raw, (size_t)bytes));
       // start a whole number of 1 KiB fragments from the factor buffer
       const uintptr_t raw = reinterpret_cast<uintptr_t>(c->recon_raw), base = reinterpret_cast<uintptr_t>(data);
       const uintptr_t adj = (base - raw) & 1023u;
@@ -794,9 +794,10 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
     // long (kFetchRanks) and several share it (kFetchGang): from there on it costs
     // 0-3% on factors that sit in the last-level cache and gains 2-20% on ones that
     // do not (7B layer, 8 requests, mean rank 582, gang of 4: 44.9 / 83.5 -> 44.9 /
-    // 73.2 us, 1M tokens, 650, gang of 10: 1463 / 1492 -> 1381 / 1374); at mean ranks
-    // of 30-250 it loses 2-6% and 0-5%, in gangs of two it gains nothing.
-    constexpr int kFetchRanks = 512, kFetchGang = 4;
+    // 73.2 us, 1M tokens, 650, gang of 10: 1463 / 1492 -> 1381 / 1374, 7B layer, 32
+    // requests, 356, three layers in turn: 207 -> 193); at mean ranks of 30-250 it
+    // loses 2-6% and 0-5%, in gangs of two it gains nothing.
+    constexpr int kFetchRanks = 320, kFetchGang = 4;
     const int max_rt = sch.max_own <= 2 ? 2 : sch.max_own == 3 ? 3 : 4;
     const bool fetch = max_rt > 2 || (sch.gang >= kFetchGang && sch.mean_ranks >= kFetchRanks);
     const size_t base = attend_lds_base_bytes(c->d, sch.rk_pad_max, sch.rv_pad_max, sch.half_w);

@@ -416,10 +416,6 @@ struct WgProgram {
   int32_t pad;
 };
 static_assert(sizeof(WgProgram) == 24, "program entry layout");
-// Bytes the attention kernel's fragment loads may read past the end of a run:
-// the factor and reconstruction buffers are allocated that much longer.
-constexpr int kOverread = 8 * 1024;
-
 // Attention kernel geometry.
 constexpr int kThreads = 64 * kWaves;
 constexpr int kCols = 64;                      // query columns per workgroup

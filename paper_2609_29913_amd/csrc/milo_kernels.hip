@@ -88,7 +88,9 @@ __device__ __forceinline__ int opaque(int v) {
 }
 
 // ends x's life without an instruction: its registers are free until the next write
-__device__ __forceinline__ void forget(bf16x8& x) { asm volatile("" : "=v"(x)); }
+template <typename T>
+__device__ __forceinline__ void forget(T& x) { asm volatile("" : "=v"(x)); }
+__device__ __forceinline__ void forget(uint2& x) { asm volatile("" : "=v"(x.x), "=v"(x.y)); }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -375,8 +377,9 @@ __device__ __forceinline__ WorkItem lds_item(const unsigned char* p) {
 // is what lets the compiler wait for the slot in use alone (s_waitcnt vmcnt
 // counts in order).  The set sizes are what the registers hold without a spill:
 // a spilled value's scratch loads sit in the same in-order count and stop the
-// streams.  Reloads may read past a run: at most kOverread bytes, which the
-// buffers' allocations cover.
+// streams.  A run's loads go through a buffer that ends with it, so the slots a
+// short run leaves out read nothing (7B layer of 32 requests 193 -> 191 us, prefill
+// of 45 tokens 84.4 -> 82.7, against reading on).
 // (Streaming through per-wave LDS rings by direct global->LDS loads, as this
 // kernel did before, cost two LDS passes and ~16 scalar instructions per
 // fragment.)
@@ -388,12 +391,15 @@ __device__ __forceinline__ WorkItem lds_item(const unsigned char* p) {
 // (Two tiles per step, which halves the LDS reads per score, was measured too: the
 // registers it takes send the group's output through memory, and it gained 2-5% on
 // long items and lost up to 14% on short ones.)
-template <int D>
+// INT8 P factors: a slot holds the 8 codes of a lane, half the bytes, so there are
+// twice as many where registers allow (four left 2 KiB of a wave's codes in flight:
+// 7B layer of 8 requests 56.0 -> 52.4 us); R^K, which is bf16, has registers of its own.
+template <bool I8, int MAX_RT>
 struct Streams {
-  static constexpr int KD = 4;  // steps in a round of ks
-  static constexpr int VD = 4;  // P^V fragments loaded ahead across tiles
-  static_assert(KD * 1024 <= kOverread, "reads past a run stay inside its buffer");
-  bf16x8 ks[KD], vs[VD];
+  using Slot = std::conditional_t<I8, uint2, bf16x8>;
+  static constexpr int KD = I8 && MAX_RT < 4 ? 8 : 4;  // steps in a round of ks
+  static constexpr int VD = KD;  // P^V fragments loaded ahead across tiles
+  Slot ks[KD], vs[VD];
 };
 
 // f(integral constant i) for i = FROM, FROM + STEP, .. below TO
@@ -408,7 +414,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // A wave-uniform fragment address p + off loaded by every lane: buffer loads
 // take the base and offset in scalar registers, the lane's part in one vector
 // register.  wanted is -1, or 0: nothing is read (an empty buffer), the slot
-// gets zeros; as arithmetic on a scalar it costs no branch in the loops.
+// gets zeros; or the bytes of p's run, past which nothing is read either; as
+// arithmetic on a scalar it costs no branch in the loops.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t frag_buffer(const unsigned char* p, int wanted) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(p), 0, __builtin_amdgcn_readfirstlane(wanted),
                                            0x00020000);
@@ -432,8 +439,8 @@ __device__ __forceinline__ void pin_load() { __builtin_amdgcn_sched_barrier(0x00
 template <int N, int B>
 struct RunStart {
   const unsigned char* p;
-  int odd, wanted;
-  __device__ __forceinline__ RunStart(const unsigned char* p_, int n) : p(p_), odd(n & (N - 1)), wanted(mask_lt(0, n)) {}
+  int odd, wanted;  // wanted: the bytes of the run
+  __device__ __forceinline__ RunStart(const unsigned char* p_, int n) : p(p_), odd(n & (N - 1)), wanted(n * B) {}
   __device__ __forceinline__ int off(int s) const { return (s + odd - (s + odd >= N ? N : 0)) * B; }
 };
 // Consume a run of n steps (an even number) at p through slots 0 .. N-1: use(f, s)
@@ -453,7 +460,7 @@ __device__ __forceinline__ void consume_run(const unsigned char* p, int n, const
       static_for<0, N - ODD, 1>([&](auto s) { load(s, next.p, next.off(s), next.wanted); });
     }
     const unsigned char* q = more ? p : next.p;
-    const int wanted = mask_lt(N - 1, n) | next.wanted;
+    const int wanted = more ? n * B : next.wanted;
     static_for<N - ODD, N, 1>([&](auto s) {
       use(ODD - N, s);
       load(s, q, more ? (ODD + s) * B : next.off(s), wanted);
@@ -462,7 +469,7 @@ __device__ __forceinline__ void consume_run(const unsigned char* p, int n, const
 #pragma clang loop unroll(disable)
   for (int f = odd; f < n; f += N) {
     const bool last = f + N >= n;
-    const int wanted = mask_lt(f + N, n) | next.wanted;
+    const int wanted = last ? next.wanted : n * B;
     const unsigned char* q = last ? next.p : p;
     const int lo = last ? next.odd * B : (f + N) * B, hi = last ? lo - N * B : lo, wrap = N - next.odd;
     static_for<0, N, 1>([&](auto s) {
@@ -475,13 +482,12 @@ __device__ __forceinline__ void consume_run(const unsigned char* p, int n, const
 
 // The first run of a block item (bf16 P factors) for wave `wave`, at p: R^K if
 // the wave owns projection rank tiles, else the first tile's P^K
-template <int D>
-__device__ __forceinline__ RunStart<Streams<D>::KD, kFragElems * 2> item_first_run(const WorkItem* it, int wave,
+__device__ __forceinline__ RunStart<Streams<false, 2>::KD, kFragElems * 2> item_first_run(const WorkItem* it, int wave,
                                                                                    const unsigned char* p) {
   const int rk_pad = __builtin_amdgcn_readfirstlane(it->blk.rk_pad);
   const bool dense = (__builtin_amdgcn_readfirstlane(it->flags) & kItemDense) != 0;
   const bool rk = !dense && owned_tiles(rk_pad >> 5, wave, kWaves) > 0;
-  return RunStart<Streams<D>::KD, kFragElems * 2>(p, rk ? Streams<D>::KD : rk_pad >> 4);
+  return RunStart<Streams<false, 2>::KD, kFragElems * 2>(p, rk ? Streams<false, 2>::KD : rk_pad >> 4);
 }
 
 // The waves' run lists: for each of its block items a wave finds the first
@@ -599,13 +605,14 @@ __device__ __forceinline__ void load_queries(const AttendArgs& a, int c0, int cn
 // FETCH: the gang's workgroups fetch the coming tile's P into L2 between them
 template <int D, int MAX_RT, bool FETCH, int MODE>
 __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& it, unsigned char* smem,
-                                           Streams<D>& fs, RunList& rl, RunDeriver<D>& rd,
+                                           Streams<MODE == 1, MAX_RT>& fs, RunList& rl, RunDeriver<D>& rd,
                                            GroupAcc<up_col_blocks<D>()>& acc, bf16x8 (&qv)[query_loads<D>()], const WorkItem* next_item,
                                            const int tid) {
   constexpr bool I8 = MODE == 1, GV = MODE == 2;
   constexpr int NK = D / 16;
-  constexpr int KD = Streams<D>::KD, VD = Streams<D>::VD;
-  static_assert(NK == KD || NK == 2 * KD, "an R^K rank tile is one or two rounds");
+  constexpr int KD = Streams<I8, MAX_RT>::KD, VD = Streams<I8, MAX_RT>::VD;
+  using Slot = typename Streams<I8, MAX_RT>::Slot;
+  static_assert(I8 || NK == KD || NK == 2 * KD, "an R^K rank tile is one or two rounds");
   const BlockMeta& bm = it.blk;
   const int slot = it.slot, g0 = it.g, c0 = it.req;
   const int cn = ((it.flags >> kItemColsShift) & 63) + 1;  // columns of the tile
@@ -667,21 +674,13 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
     return load_frag16(p, off, lane16, wanted);
   };
   // a P^K / P^V fragment: bf16, or int8 codes (converted exactly as they are used)
-  auto ldp = [&](const unsigned char* p, int off, int wanted = -1) {
-    if constexpr (I8) {
-      const uint2 v = load_frag8(p, off, lane16 >> 1, wanted);
-      return __builtin_bit_cast(bf16x8, make_uint4(v.x, v.y, 0, 0));
-    } else {
-      return load_frag16(p, off, lane16, wanted);
-    }
+  auto ldp = [&](const unsigned char* p, int off, int wanted = -1) -> Slot {
+    if constexpr (I8) return load_frag8(p, off, lane16 >> 1, wanted);
+    else return load_frag16(p, off, lane16, wanted);
   };
-  auto use_p = [&](const bf16x8& x) {
-    if constexpr (I8) {
-      const uint4 v = __builtin_bit_cast(uint4, x);
-      return i8_to_bf16x8(make_uint2(v.x, v.y));
-    } else {
-      return x;
-    }
+  auto use_p = [&](const Slot& x) -> bf16x8 {
+    if constexpr (I8) return i8_to_bf16x8(x);
+    else return x;
   };
   // f(rank tiles this wave owns in the value pass, 16-token steps in a round of
   // it), as integral constants: a round is up to eight fragments, the first VD
@@ -713,25 +712,22 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
   constexpr int kRowChunks = D / 8;  // 16-byte chunks per query row
   constexpr int kQLoads = query_loads<D>();
   __bf16* qimg = wl;
-  constexpr bool kMoreRk = NK > KD;  // steps KD .. of an R^K rank tile
-  bf16x8 rk_more[kMoreRk ? KD : 1];
+  // steps kRkSlots .. of an R^K rank tile (those before sit in ks; INT8: none do)
+  constexpr int kRkSlots = I8 ? 0 : KD, kMoreRk = NK - kRkSlots;
+  bf16x8 rk_more[kMoreRk > 0 ? kMoreRk : 1];
   {
 #pragma unroll
     for (int u = 0; u < kQLoads; ++u) {
       const unsigned x = opaque(tid) + u * kThreads, cl = x / kRowChunks, j = x % kRowChunks;
       *reinterpret_cast<bf16x8*>(qimg + cl * D + 8 * (j ^ (cl % kRowChunks))) = qv[u];
     }
-    if constexpr (I8) {
-      // the previous item could not load this one's first K run (its element size may differ)
-      static_for<0, KD, 1>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        if (n_rk > 0) fs.ks[i] = ldf(rkp, i * kFragBytes);
-        else fs.ks[i] = ldp(pk_first.p, pk_first.off(i));
-      });
-    }
-    // the rest of the first R^K rank tile, then the first tile's P^V
-    if constexpr (kMoreRk)
-      static_for<0, KD, 1>([&](auto i) { rk_more[decltype(i)::value] = ldf(rkp, (i + KD) * kFragBytes, mask_lt(0, n_rk)); });
+    // the rest of the first R^K rank tile, then (INT8: the previous item could not
+    // load it) the first tile's P^K, then its P^V
+    static_for<0, kMoreRk, 1>([&](auto i) {
+      rk_more[decltype(i)::value] = ldf(rkp, (i + kRkSlots) * kFragBytes, mask_lt(0, n_rk));
+    });
+    if constexpr (I8)
+      static_for<0, KD, 1>([&](auto i) { fs.ks[decltype(i)::value] = ldp(pk_first.p, pk_first.off(i), pk_first.wanted); });
     static_for<0, VD, 1>([&](auto x) { forget(fs.vs[decltype(x)::value]); });
     with_own([&](auto own_c, auto cs_c) {
       constexpr int n = decltype(own_c)::value * decltype(cs_c)::value;
@@ -744,7 +740,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
   auto load_pk_first = [&]() {
     static_for<0, KD, 1>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
-      fs.ks[i] = ldp(pk_first.p, pk_first.off(i));
+      fs.ks[i] = ldp(pk_first.p, pk_first.off(i), pk_first.wanted);
     });
   };
   // ---- projection: Qt[rank][col] (stored [col][rank]), once per KV head of
@@ -820,19 +816,20 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       // each step's slot is reloaded with the same step of the next rank tile (the
       // next head's run starts nrt_k NK fragments on; past the last, P^K)
       const unsigned char* after = rkp + (j + 1 < own_k ? (int64_t)hh * nrt_k + j + 1 : (int64_t)(hh + 1) * nrt_k) * NK * kFragBytes;
-      const bool to_pk = !I8 && x + 1 == nx;
+      const bool to_pk = x + 1 == nx;
       f32x16 acc0 = zero16(), acc1 = zero16();
       static_for<0, NK, 1>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        if constexpr (k >= KD) {
-          acc0 = mfma32(rk_more[k - KD], qf[k][0], acc0);
-          acc1 = mfma32(rk_more[k - KD], qf[k][1], acc1);
-          rk_more[k - KD] = ldf(after, k * kFragBytes, mask_lt(x + 1, nx));
-        } else {
+        if constexpr (k >= kRkSlots) {
+          bf16x8& slot = rk_more[k - kRkSlots];
+          acc0 = mfma32(slot, qf[k][0], acc0);
+          acc1 = mfma32(slot, qf[k][1], acc1);
+          slot = ldf(after, k * kFragBytes, mask_lt(x + 1, nx));
+        } else if constexpr (!I8) {
           acc0 = mfma32(fs.ks[k], qf[k][0], acc0);
           acc1 = mfma32(fs.ks[k], qf[k][1], acc1);
           fs.ks[k] = ldf(to_pk ? pk_first.p : after, to_pk ? pk_first.off(k) : k * kFragBytes,
-                         to_pk ? -1 : mask_lt(x + 1, nx));
+                         to_pk ? pk_first.wanted : mask_lt(x + 1, nx));
         }
       });
 #pragma unroll
@@ -849,7 +846,6 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
       }
       if (++j == own_k) j = 0, ++hh;
     }
-    if constexpr (I8) load_pk_first();
   }
   lds_barrier();
 
@@ -912,7 +908,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
         if (after >= ntiles) {
           kn.wanted = 0;
           if constexpr (!I8)
-            if (next_item) kn = item_first_run<D>(next_item, wave, data + (int64_t)rl.next_first() * kPBytes);
+            if (next_item) kn = item_first_run(next_item, wave, data + (int64_t)rl.next_first() * kPBytes);
         }
         auto use = [&](int f, auto slot) {
           constexpr int i = decltype(slot)::value;
@@ -1035,7 +1031,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
         // then the next tile's; the slots past VD hold a step's fragments only
         // here (the scores' registers are free)
         constexpr int NF = CS * OWN;  // fragments in a round
-        bf16x8 vx[NF > VD ? NF - VD : 1];
+        Slot vx[NF > VD ? NF - VD : 1];
         const unsigned char* vb = pvp + (int64_t)tt * 16 * OWN * kPBytes;
         static_for<VD, NF, 1>([&](auto x) { vx[decltype(x)::value - VD] = ldp(vb, x * kPBytes); });
         lds_barrier();
@@ -1062,7 +1058,7 @@ __device__ __forceinline__ void block_item(const AttendArgs& a, const WorkItem& 
             const bf16x8 w0 = ld_bf16x8(wr0 + 16 * st + 16 * i), w1 = ld_bf16x8(wr1 + 16 * st + 16 * i);
             static_for<0, OWN, 1>([&](auto rc) {
               constexpr int r = decltype(rc)::value, x = i * OWN + r;
-              bf16x8& slot = [&]() -> bf16x8& {
+              Slot& slot = [&]() -> Slot& {
                 if constexpr (x < VD) return fs.vs[x];
                 else return vx[x - VD];
               }();
@@ -1319,7 +1315,7 @@ __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
   lds_barrier();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned char* work = smem + a.prog_bytes;
-  Streams<D> fs;
+  Streams<MODE == 1, MAX_RT> fs;
   GroupAcc<up_col_blocks<D>()> acc;
   RunDeriver<D> rd;
   rd.items = smem;
@@ -1347,11 +1343,11 @@ __global__ __launch_bounds__(kThreads, 1) void attend_kernel(AttendArgs a) {
     load_queries<D>(a, c0, ((fl >> kItemColsShift) & 63) + 1, threadIdx.x, qv);
     if constexpr (MODE != 1) {  // INT8 items load their first K run themselves
       const int lane16 = 16 * (threadIdx.x & 63);
-      const auto run = item_first_run<D>(it, wave, reinterpret_cast<const unsigned char*>(a.data) +
+      const auto run = item_first_run(it, wave, reinterpret_cast<const unsigned char*>(a.data) +
                                                        (int64_t)rl.first(0) * kFragElems * 2);
-      static_for<0, Streams<D>::KD, 1>([&](auto ic) {
+      static_for<0, Streams<false, 2>::KD, 1>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
-        fs.ks[i] = load_frag16(run.p, run.off(i), lane16);
+        fs.ks[i] = load_frag16(run.p, run.off(i), lane16, run.wanted);
       });
     }
   }

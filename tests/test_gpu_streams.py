@@ -69,8 +69,8 @@ MORE = {
                  n_kv_heads=2, head_dim=128, n_q=2, n_q_heads=10),
     "fold_d64": dict(block_tokens=[100, 256, 300] * 200, rank_k=[17, 64, 96] * 200, rank_v=[32, 96, 20] * 200,
                      n_kv_heads=2, head_dim=64, n_q=2, n_q_heads=10),
-    # gangs of ten on either side of the mean rank (rk + rv = 512) from which they fetch
-    "gang_low": dict(block_tokens=[1100, 256, 769, 1000], rank_k=[96, 250, 128, 200], n_kv_heads=8, head_dim=128,
+    # gangs of ten on either side of the mean rank (rk + rv = 320) from which they fetch
+    "gang_low": dict(block_tokens=[1100, 256, 769, 1000], rank_k=[96, 250, 128, 100], n_kv_heads=8, head_dim=128,
                      n_q=16, n_q_heads=40),
     "gang_fetch": dict(block_tokens=[1100, 288, 769, 1000], rank_k=[320, 256, 500, 288], n_kv_heads=8, head_dim=128,
                        n_q=16, n_q_heads=40),
