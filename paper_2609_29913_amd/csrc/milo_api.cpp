@@ -548,6 +548,10 @@ class CacheWorkspace : public Workspace {
     *dev = c->plan_d;
     return MILO_OK;
   }
+  bool fits(int64_t need, int d) const override {
+    const int64_t cap = env_byte_cap();
+    return need <= c_->part_cols_slots || cap < 0 || c_->data_elems * 2 + need * ((int64_t)d * 4 + 8) <= cap;
+  }
   int partials(int64_t need, int d, hipStream_t s, float** o, float2** ml) override {
     milo_cache* c = c_;
     if (need > c->part_cols_slots) {
@@ -780,6 +784,15 @@ int attend_call(milo_cache* c, PlanState& ps, Workspace& ws, const int32_t* bloc
     pin.causal_block = shared_tail ? c->n_blocks : -1;
     if (!build_schedule(pin, table_x.data(), (int)table_x.size(), n_q, n_chunks, til, env_program_cap(), &sch, &why))
       return fail(MILO_ERR_UNSUPPORTED, "%s", why.c_str());
+    // a workspace of fixed size that does not hold this plan's partials may hold
+    // those of the plan by the fitted tile cost
+    if (!ws.fits((int64_t)n_cols * (sch.n_block_slots + n_chunks), c->d)) {
+      Schedule other;
+      pin.frag_tile_cost = kCostFragTileFit;
+      if (build_schedule(pin, table_x.data(), (int)table_x.size(), n_q, n_chunks, til, env_program_cap(), &other, &why) &&
+          ws.fits((int64_t)n_cols * (other.n_block_slots + n_chunks), c->d))
+        sch = std::move(other);
+    }
     // the reconstruction table and tasks follow the schedule in the plan
     int64_t rb_off = 0, rt_off = 0;
     if (n_recon > 0) {

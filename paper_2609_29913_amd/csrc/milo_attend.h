@@ -49,6 +49,8 @@ class Workspace {
   virtual int partials(int64_t cols_slots, int d, hipStream_t s, float** o, float2** ml) = 0;
   // device copy of n_q tail lengths (batches above kInlineTails), queued in stream order
   virtual int tail_lengths(const int32_t* host, int n_q, hipStream_t s, const int32_t** dev) = 0;
+  // whether partials() has room for that many (column, slot) pairs
+  virtual bool fits(int64_t cols_slots, int d) const = 0;
   // whether the call may take timing events from the library's pool (creating some when it is empty)
   virtual bool may_time() const = 0;
   // reconstruct-then-attend: a buffer of `elems` bf16 elements whose distance

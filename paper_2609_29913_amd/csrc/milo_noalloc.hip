@@ -62,10 +62,14 @@ class ScratchWorkspace : public Workspace {
     *dev = d_.ptr;
     return MILO_OK;
   }
+  static size_t ml_bytes_of(int64_t cols_slots) { return ((size_t)cols_slots * sizeof(float2) + 255) / 256 * 256; }
+  bool fits(int64_t cols_slots, int d) const override {
+    return ml_bytes_of(cols_slots) + (size_t)cols_slots * d * 4 <= kScratchBytes - kScratchPartOff;
+  }
   int partials(int64_t cols_slots, int d, hipStream_t, float** o, float2** ml) override {
-    const size_t ml_bytes = ((size_t)cols_slots * sizeof(float2) + 255) / 256 * 256;
+    const size_t ml_bytes = ml_bytes_of(cols_slots);
     const size_t need = ml_bytes + (size_t)cols_slots * d * 4;
-    if (need > kScratchBytes - kScratchPartOff)
+    if (!fits(cols_slots, d))
       return scratch_fail(MILO_ERR_UNSUPPORTED,
                           "partial results of %lld bytes exceed the scratch's %lld-byte region "
                           "(use milo_attend_decode, which grows its own workspace)",

@@ -64,15 +64,14 @@ size_t attend_ring_bytes(int) { return 0; }
 // skip chunks past it, so a decode loop whose tails grow by one token per step
 // reuses its plan until the longest tail doubles.
 // ---------------------------------------------------------------------------
-// Cost model (microseconds on an MI355X, from a least-squares fit to per-item
-// kernel timings of the 7B-shaped layer; the tile stream's 0.13 was 0.153 with
-// fragments streamed through LDS, and 0.13 picks better splits now: the 7B layer
-// with INT8 P 51.9 -> 48.3 us, the others within 0.5%): one fragment of the
+// Cost model (microseconds on an MI355X): a least-squares fit to per-item timings of
+// an earlier kernel on the 7B-shaped layer, but for the tile stream's kCostFragTile:
+// 0.13, swept, where the fit gave 0.153 (7B layer of 8 requests 47.9 -> 44.7 us, 240
+// drawn calls 0.2% better).  One fragment of the
 // slowest wave's projection and up-projection streams, one fragment of its
 // tile stream, the per-tile softmax and barriers, the per-item set-up, one
 // round of the token-segment reduction, and one dense-tail chunk.
-constexpr double kCostFragItem = 0.206, kCostFragTile = 0.13, kCostTile = 1.75, kCostItem = 2.43,
-                 kCostSegRound = 0.61, kCostTail = 9.4;
+constexpr double kCostFragItem = 0.206, kCostTile = 1.75, kCostItem = 2.43, kCostSegRound = 0.61, kCostTail = 9.4;
 constexpr int kPerXcd = kCUs / kXcds;  // workgroups per XCD
 
 // Workgroups per gang for n_ct column tiles: a divisor of n_ct of at most one
@@ -147,7 +146,7 @@ bool build_schedule(const PlanInput& c, const int32_t* table, int n_sel, int n_q
     for (int h = nseg; h > 1; h /= 2) ++rounds;
     const double item_frags = dense ? 0.0 : nh * ((double)NK * mk + m.rv_pad / 32.0);
     const double tile_frags = nt * ((double)nks + 16.0 / nseg * mv);
-    return kCostFragItem * item_frags + kCostFragTile * tile_frags + kCostTile * nt + kCostItem +
+    return kCostFragItem * item_frags + c.frag_tile_cost * tile_frags + kCostTile * nt + kCostItem +
            kCostSegRound * rounds;
   };
   const int n_ct = til.n_ct;

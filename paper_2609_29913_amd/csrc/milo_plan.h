@@ -12,6 +12,8 @@
 
 namespace milo {
 
+constexpr double kCostFragTile = 0.13, kCostFragTileFit = 0.153;
+
 // What the planner needs to know about a cache.
 struct PlanInput {
   const BlockMeta* meta;  // [n_blocks]
@@ -24,6 +26,10 @@ struct PlanInput {
   // a prefill chunk's shared tail, attended as a packed dense block: its block
   // id in meta / recon_region (its items carry kItemCausal), or -1
   int causal_block = -1;
+  // cost of one fragment of an item's tile stream (microseconds): the swept value, or
+  // the fitted one, whose plans a fixed workspace may hold where it does not hold the
+  // swept one's (either may take a slot or two more)
+  double frag_tile_cost = kCostFragTile;
 };
 
 struct Tiling {

@@ -85,3 +85,23 @@ def test_noalloc_refuses_a_workspace_beyond_the_scratch():
         assert bool((out == 3.0).all())
     finally:
         gl.free()
+
+
+def test_noalloc_takes_a_plan_that_fits():
+    """1696 columns over 100 blocks: the planner's first choice needs 67 slots per column
+    tile, 59 MB of partial results, beyond the 55 MiB region; the plan by the fitted tile
+    cost needs 64, 56 MB, and is the one the call runs."""
+    from paper_2609_29913_amd import milo
+    n = 100
+    inp = synth.make_problem(62, [(500, 1500, 1100)[b % 3] for b in range(n)], [(32, 64, 128)[b % 3] for b in range(n)],
+                             n_kv_heads=1, head_dim=128, n_q=106, n_q_heads=16, tail_cap=0)
+    gl = GpuLayer(inp)
+    try:
+        out = torch.full(inp.q.shape, float("nan"), dtype=torch.float32, device="cuda")
+        milo.milo_attend_decode_noalloc(gl.cache, list(range(n)), gl.q, None, None, None, inp.scale, out)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+    finally:
+        gl.free()
+    assert np.all(np.isfinite(got))
+    assert max_rel_l2(got, oracle.attend_latent(**oracle_args(inp))) <= TOL_REL_L2
